@@ -21,4 +21,6 @@ struct BvhHost {
 
 bool build_bvh(const float* vertices, int32_t nv, const int32_t* tris, int32_t nt, BvhHost& out);
 
+constexpr int32_t kBvhEmpty = 0x7FFFFFFF;  // device nodes: no child in this slot
+
 }  // namespace neb

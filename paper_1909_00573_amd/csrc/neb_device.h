@@ -1,6 +1,7 @@
 // Device helpers of libneb: vector math, Philox, BSDFs, plane-box area,
 // octree addressing and queries, BVH traversal.  gfx950 only.
 #pragma once
+#include "neb_bvh.h"
 #include "neb_internal.h"
 
 namespace neb {
@@ -425,7 +426,7 @@ __device__ __forceinline__ RayPre ray_pre(f3 o, f3 d) {
     float dz = get3(d, kz);
     r.sx = get3(d, kx) / dz;
     r.sy = get3(d, ky) / dz;
-    r.sz = 1.0f / dz;
+    r.sz = fabsf(dz) > 1e-30f ? get3(r.inv, kz) : 1.0f / dz;
     return r;
 }
 
@@ -452,42 +453,57 @@ __device__ __forceinline__ float tri_hit(const RayPre& r, f3 v0, f3 v1, f3 v2, f
     return (t > 0.f && t < tmax) ? t : -1.f;
 }
 
-__device__ __forceinline__ bool box_hit(const RayPre& r, float lx, float ly, float lz, float hx, float hy,
-                                        float hz, float tmax, float& tn) {
-    float t0x = (lx - r.o.x) * r.inv.x, t1x = (hx - r.o.x) * r.inv.x;
-    float t0y = (ly - r.o.y) * r.inv.y, t1y = (hy - r.o.y) * r.inv.y;
-    float t0z = (lz - r.o.z) * r.inv.z, t1z = (hz - r.o.z) * r.inv.z;
-    float tnear = fmaxf(fmaxf(fminf(t0x, t1x), fminf(t0y, t1y)), fmaxf(fminf(t0z, t1z), 0.0f));
-    float tfar = fminf(fminf(fmaxf(t0x, t1x), fmaxf(t0y, t1y)), fminf(fmaxf(t0z, t1z), tmax));
-    tn = tnear;
-    return tnear <= tfar * 1.00000024f;
-}
-
-// Resumable closest-hit traversal: the state of one ray, advanced by up to
-// max_steps node visits per call, so a lane whose ray ends can take a new
-// one while the rest of its wave is still traversing.  Ties on t go to the
-// lowest primitive id; the stack is the lane's kStack LDS slots, stride
-// kTraceBlock (the BVH's stack need must be below kStack); kAnyHit stops at
-// the first hit below tmax.
+// Closest-hit traversal, one ray per lane, in two kinds of step that the
+// caller (k_extend) runs for the lanes that wait for them: trace_node picks
+// the lane's next inner node and tests its four children's boxes, then
+// trace_triangle tests the triangles of the leaves among them one at a time,
+// slot by slot, before the next trace_node stacks the inner children still in
+// reach, nearest on top.  The order is that of a walk of one ray by itself.
+// Ties on t go to the lowest primitive id; the stack is the lane's LDS slots
+// (stride kTraceBlock, slot 0 never filled).
 struct TraceState {
     RayPre r;
+    // byte offsets in a node of the words with the ray's near and far planes
+    // of each axis (low planes: words 0..2, high ones 3..5)
+    uint32_t nx, ny, nz, fx, fy, fz;
     float best;
     int prim;
-    int node;
-    int sp;
+    // the last visited node's children: references (a node, ~ a leaf's first
+    // triangle, kBvhEmpty) and the distance of an inner child in reach, -1
+    // for a leaf in reach whose triangles are still to test, else INFINITY
+    int c0, c1, c2, c3;
+    float d0, d1, d2, d3;
+    float least;  // the smallest of the four: < 0 while triangles come first
+    int tri;      // the next triangle of the leaf in hand (the first slot with distance -1), -1: its first
+    int* top;     // topmost filled stack slot; bot: none is filled
+    int* bot;     // the slot below its lowest filled one
 };
 
-__device__ __forceinline__ void trace_begin(TraceState& T, int root, f3 o, f3 d, float tmax = INFINITY) {
+// the lane's walk starts (or goes on, with another lane's ray) at node `from`
+__device__ __forceinline__ void trace_at(TraceState& T, int from, int* stack) {
+    T.nx = T.r.inv.x < 0.f ? 48u : 0u;
+    T.ny = T.r.inv.y < 0.f ? 64u : 16u;
+    T.nz = T.r.inv.z < 0.f ? 80u : 32u;
+    T.fx = 48u - T.nx;
+    T.fy = 80u - T.ny;
+    T.fz = 112u - T.nz;
+    T.d0 = T.least = 0.f;
+    T.d1 = T.d2 = T.d3 = INFINITY;
+    T.c0 = from;
+    T.tri = -1;
+    T.top = T.bot = stack;
+}
+
+// false: a ray that cannot hit anything (a NaN among its numbers, or no
+// length), which the walk must not see: only there could it enter an empty slot
+__device__ __forceinline__ bool trace_begin(TraceState& T, int root, int* stack, f3 o, f3 d, float tmax = INFINITY) {
     T.r = ray_pre(o, d);
     T.best = tmax;
     T.prim = -1;
-    T.node = root;
-    T.sp = 0;
+    trace_at(T, root, stack);
+    return tmax > 0.f && o.x + o.y + o.z + (d.x + d.y + d.z) == o.x + o.y + o.z + (d.x + d.y + d.z);
 }
 
-// returns true when the ray is done (T.best, T.prim hold the closest hit
-// below the tmax of trace_begin; kAnyHit: T.prim >= 0 once any hit below
-// tmax is found, which ends the ray)
 // (distance, node) pair of a child still to visit; compare-exchange by distance
 __device__ __forceinline__ void near_first(float& da, int& na, float& db, int& nb) {
     const bool sw = db < da;
@@ -499,82 +515,90 @@ __device__ __forceinline__ void near_first(float& da, int& na, float& db, int& n
     na = n;
 }
 
-template <int kStack, bool kAnyHit = false>
-__device__ __forceinline__ bool trace_steps(const SceneView& S, TraceState& T, int* stack, int max_steps,
-                                            unsigned& nodes, unsigned& tris) {
+// 16 bytes at a byte offset of a pool (Off: 32 bits where the pool is below
+// 4 GB, which spares the 64-bit address arithmetic)
+template <typename Off>
+__device__ __forceinline__ float4 pool16(const float4* base, Off byte) {
+    return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(base) + byte);
+}
+
+// One node step.  The near and far planes are loaded by the ray's direction
+// signs, so a slab needs no minimum and maximum of its two distances.  An
+// empty slot's planes lie the wrong way round (1e30 before -1e30), out of
+// every ray's reach.  Returns false when no node is left: the ray is done.
+template <typename Off>
+__device__ __forceinline__ bool trace_node(const SceneView& S, TraceState& T) {
     const RayPre& r = T.r;
-    for (int step = 0; step < max_steps; ++step) {
-        // one 128-byte node: the four children's boxes coordinate by
-        // coordinate, their links and leaf counts
-        const float4* nd = S.bvh + 8 * T.node;
-        ++nodes;
-        const float4 lx = nd[0], ly = nd[1], lz = nd[2], hx = nd[3], hy = nd[4], hz = nd[5];
-        const int4 lk = *reinterpret_cast<const int4*>(nd + 6);
-        const int4 ct = *reinterpret_cast<const int4*>(nd + 7);
-        float t0, t1, t2, t3;
-        const bool h0 = box_hit(r, lx.x, ly.x, lz.x, hx.x, hy.x, hz.x, T.best, t0) && lk.x >= 0;
-        const bool h1 = box_hit(r, lx.y, ly.y, lz.y, hx.y, hy.y, hz.y, T.best, t1) && lk.y >= 0;
-        const bool h2 = box_hit(r, lx.z, ly.z, lz.z, hx.z, hy.z, hz.z, T.best, t2) && lk.z >= 0;
-        const bool h3 = box_hit(r, lx.w, ly.w, lz.w, hx.w, hy.w, hz.w, T.best, t3) && lk.w >= 0;
-        // the hit leaf children's triangles in one loop, each triangle's
-        // three words loaded one iteration ahead of its test, so that the
-        // leaves of a node cost one load latency, not one per triangle
-        const int n0 = (h0 && ct.x > 0) ? ct.x : 0, n1 = (h1 && ct.y > 0) ? ct.y : 0;
-        const int n2 = (h2 && ct.z > 0) ? ct.z : 0, n3 = (h3 && ct.w > 0) ? ct.w : 0;
-        const int e0 = n0, e1 = e0 + n1, e2 = e1 + n2, nt = e2 + n3;
-        if (nt > 0) {
-            tris += nt;
-            // m-th triangle of the hit leaves, slot by slot
-            auto tri_of = [&](int m) {
-                return m < e0 ? lk.x + m : (m < e1 ? lk.y + (m - e0) : (m < e2 ? lk.z + (m - e1) : lk.w + (m - e2)));
-            };
-            const float4* tp = S.tri + 3 * tri_of(0);
-            float4 p0 = tp[0], p1 = tp[1], p2 = tp[2];
-            for (int m = 0; m < nt; ++m) {
-                float4 q0 = p0, q1 = p1, q2 = p2;
-                if (m + 1 < nt) {
-                    const float4* tq = S.tri + 3 * tri_of(m + 1);
-                    q0 = tq[0];
-                    q1 = tq[1];
-                    q2 = tq[2];
-                }
-                float t = tri_hit(r, xyz(p0), xyz(p1), xyz(p2), kAnyHit ? T.best : T.best * 1.0000001f);
-                int id = __float_as_int(p0.w);
-                if (t > 0.f && (t < T.best || (t == T.best && id < T.prim))) {
-                    T.best = t;
-                    T.prim = id;
-                    if (kAnyHit) return true;
-                }
-                p0 = q0;
-                p1 = q1;
-                p2 = q2;
-            }
-        }
-        // inner children still in reach, sorted nearest first (five
-        // compare-exchanges); the nearest is next, the others are pushed
-        // farthest first
-        float d0 = (h0 && ct.x == 0 && t0 < T.best) ? t0 : INFINITY;
-        float d1 = (h1 && ct.y == 0 && t1 < T.best) ? t1 : INFINITY;
-        float d2 = (h2 && ct.z == 0 && t2 < T.best) ? t2 : INFINITY;
-        float d3 = (h3 && ct.w == 0 && t3 < T.best) ? t3 : INFINITY;
-        const int k = (d0 < INFINITY) + (d1 < INFINITY) + (d2 < INFINITY) + (d3 < INFINITY);
-        if (k == 0) {
-            if (T.sp == 0) return true;
-            T.node = stack[(--T.sp) * kTraceBlock];
-            continue;
-        }
-        int c0 = lk.x, c1 = lk.y, c2 = lk.z, c3 = lk.w;
-        near_first(d0, c0, d1, c1);
-        near_first(d2, c2, d3, c3);
-        near_first(d0, c0, d2, c2);
-        near_first(d1, c1, d3, c3);
-        near_first(d1, c1, d2, c2);
-        if (k > 3 && T.sp < kStack) stack[(T.sp++) * kTraceBlock] = c3;
-        if (k > 2 && T.sp < kStack) stack[(T.sp++) * kTraceBlock] = c2;
-        if (k > 1 && T.sp < kStack) stack[(T.sp++) * kTraceBlock] = c1;
-        T.node = c0;
+    int next = *T.top;
+    // inner children still in reach, sorted nearest first (five
+    // compare-exchanges; those at or beyond the nearest hit come last and are
+    // dropped); the nearest is next, the others are stacked farthest first
+    float d0 = T.d0, d1 = T.d1, d2 = T.d2, d3 = T.d3;
+    int c0 = T.c0, c1 = T.c1, c2 = T.c2, c3 = T.c3;
+    near_first(d0, c0, d1, c1);
+    near_first(d2, c2, d3, c3);
+    near_first(d0, c0, d2, c2);
+    near_first(d1, c1, d3, c3);
+    near_first(d1, c1, d2, c2);
+    if (d3 < T.best) *(T.top += kTraceBlock) = c3;
+    if (d2 < T.best) *(T.top += kTraceBlock) = c2;
+    if (d1 < T.best) *(T.top += kTraceBlock) = c1;
+    if (d0 < T.best) {
+        next = c0;
+    } else {
+        if (T.top == T.bot) return false;
+        T.top -= kTraceBlock;
     }
-    return false;
+    const Off nd = (Off)(uint32_t)next << 7;
+    const float4 ax = pool16<Off>(S.bvh, nd + T.nx), ay = pool16<Off>(S.bvh, nd + T.ny),
+                 az = pool16<Off>(S.bvh, nd + T.nz), bx = pool16<Off>(S.bvh, nd + T.fx),
+                 by = pool16<Off>(S.bvh, nd + T.fy), bz = pool16<Off>(S.bvh, nd + T.fz),
+                 rf = pool16<Off>(S.bvh, nd + 96u);
+    auto reach = [&](float nx, float ny, float nz, float fx, float fy, float fz, int ref) {
+        const float tn = fmaxf(fmaxf((nx - r.o.x) * r.inv.x, (ny - r.o.y) * r.inv.y),
+                               fmaxf((nz - r.o.z) * r.inv.z, 0.0f));
+        const float tf = fminf(fminf((fx - r.o.x) * r.inv.x, (fy - r.o.y) * r.inv.y),
+                               fminf((fz - r.o.z) * r.inv.z, T.best));
+        return tn <= tf * 1.00000024f ? (ref < 0 ? -1.0f : tn) : INFINITY;
+    };
+    T.c0 = __float_as_int(rf.x);
+    T.c1 = __float_as_int(rf.y);
+    T.c2 = __float_as_int(rf.z);
+    T.c3 = __float_as_int(rf.w);
+    T.d0 = reach(ax.x, ay.x, az.x, bx.x, by.x, bz.x, T.c0);
+    T.d1 = reach(ax.y, ay.y, az.y, bx.y, by.y, bz.y, T.c1);
+    T.d2 = reach(ax.z, ay.z, az.z, bx.z, by.z, bz.z, T.c2);
+    T.d3 = reach(ax.w, ay.w, az.w, bx.w, by.w, bz.w, T.c3);
+    T.least = fminf(fminf(T.d0, T.d1), fminf(T.d2, T.d3));
+    return true;
+}
+
+// One triangle step; the leaf's next triangle follows unless this one is
+// marked as its last (v1.w).  kAnyHit: any hit below the ray's end finishes
+// it.  Returns false when the ray is done.
+template <bool kAnyHit, typename Off>
+__device__ __forceinline__ bool trace_triangle(const SceneView& S, TraceState& T) {
+    const bool f0 = T.d0 < 0.f, f1 = !f0 && T.d1 < 0.f, f2 = !f0 && !f1 && T.d2 < 0.f, f3 = !f0 && !f1 && !f2;
+    // (values, not a choice between the members' addresses, which would keep the state in memory)
+    const int c0 = T.c0, c1 = T.c1, c2 = T.c2, c3 = T.c3;
+    if (T.tri < 0) T.tri = ~(f0 ? c0 : f1 ? c1 : f2 ? c2 : c3);
+    const Off at = (Off)(uint32_t)T.tri * 48u;
+    const float4 p0 = pool16<Off>(S.tri, at), p1 = pool16<Off>(S.tri, at + 16u), p2 = pool16<Off>(S.tri, at + 32u);
+    const float t = tri_hit(T.r, xyz(p0), xyz(p1), xyz(p2), kAnyHit ? T.best : T.best * 1.0000001f);
+    const int id = __float_as_int(p0.w);
+    if (t > 0.f && (t < T.best || (t == T.best && id < T.prim))) {
+        T.best = t;
+        T.prim = id;
+        if (kAnyHit) return false;
+    }
+    const bool last = __float_as_int(p1.w) != 0;
+    T.tri = last ? -1 : T.tri + 1;
+    T.d0 = last && f0 ? INFINITY : T.d0;
+    T.d1 = last && f1 ? INFINITY : T.d1;
+    T.d2 = last && f2 ? INFINITY : T.d2;
+    T.d3 = last && f3 ? INFINITY : T.d3;
+    T.least = fminf(fminf(T.d0, T.d1), fminf(T.d2, T.d3));
+    return true;
 }
 
 // device-wide counter add with one atomic per wave
