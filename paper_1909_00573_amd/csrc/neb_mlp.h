@@ -34,15 +34,14 @@ struct Mlp {
     float* theta = nullptr;    // FP32 master parameters
     float* m = nullptr;        // Adam moments
     float* v = nullptr;
-    float* grad = nullptr;     // accumulated gradient (cleared by the Adam step)
     uint16_t* blob = nullptr;  // bf16 operand fragments of W1..W3
     MlpNorm* norm = nullptr;
     float* loss = nullptr;     // running sum of squared errors
     double* moments = nullptr;
-    uint16_t* acts = nullptr;  // feature-major bf16 activations and deltas of one batch
+    uint16_t* acts = nullptr;  // tile-major bf16 activations and deltas of one batch
     float* part = nullptr;     // per-wave partial sums of the small gradients and the loss
-    float* wpart = nullptr;    // per-slice partial weight gradients of W1..W3 (summed by a second launch)
-    int32_t max_batch = 0, npad = 0, max_waves = 0, max_slices = 0;
+    float* wpart = nullptr;    // per-slice parts of the last batch's gradient (summed with the Adam step)
+    int32_t max_batch = 0, max_slices = 0, slices = 0;
     int64_t step = 0;          // Adam steps taken
 };
 
@@ -59,6 +58,9 @@ hipError_t mlp_infer(const Mlp& m, const float* pos, int pos_stride, const float
 hipError_t mlp_gradient(Mlp& m, const float* pos, int pos_stride, const float* nrm, int nrm_stride,
                         const float* target, const int32_t* pool_dev, int32_t pool_host, int32_t batch, int sample,
                         uint32_t k0, uint32_t k1, const OctParams* box, hipStream_t s);
+// after mlp_gradient: one Adam step on its gradient, or the gradient itself
+// (NEB_MLP_PARAMS floats, device)
+hipError_t mlp_write_gradient(Mlp& m, float* grad, hipStream_t s);
 hipError_t mlp_adam(Mlp& m, float lr, float beta1, float beta2, float eps, hipStream_t s);
 
 }  // namespace neb

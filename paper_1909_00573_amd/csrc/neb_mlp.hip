@@ -7,22 +7,19 @@
 // -> 64 -> 64 -> 64 (ReLU) -> 1, output log rho = mu + sigma * y.
 //
 // gfx950 mapping.  The three 64-wide layers run on the matrix cores, bf16
-// operands and FP32 accumulation: inference on v_mfma_f32_16x16x32_bf16
-// (v_mfma_f32_16x16x16_bf16 for the last 16 inputs of layer 1), training
-// on v_mfma_f32_16x16x16_bf16 (its loss came out wrong with the 16 x 16 x 32
-// form in the training kernel under this toolchain, while inference with it
-// matches the reference).  A wave
-// evaluates 16 samples at a time with the transposed product
+// operands and FP32 accumulation: inference on v_mfma_f32_16x16x32_bf16,
+// training on v_mfma_f32_16x16x16_bf16.
+// A wave evaluates 16 samples at a time with the transposed product
 //     Z^T (64 x 16) = W^T (64 x K) . X^T (K x 16),
 // so the weights are the A operand and the samples the B operand.  The
 // accumulator of output block ob holds, in lane l, features 16 ob +
 // 4 (l / 16) + i (i = 0..3) of sample l % 16 -- exactly the B-operand
 // layout of the next layer's k-block ob, so layers chain in registers
 // without any transpose.  The backward data pass uses A = W the same way.
-// Weight gradients are K = batch GEMMs over feature-major bf16 stores of
-// the activations and deltas.  Weights are kept as FP32 master copies
-// (Adam) and re-packed after every step into bf16 operand fragments (each
-// lane's four values contiguous), which the kernels stage in LDS.
+// Weight gradients are K = batch GEMMs over tile-major bf16 stores of
+// the activations and deltas.  Weights are kept as
+// FP32 master copies (Adam) and re-packed after every step into bf16 operand
+// fragments, which the kernels stage in LDS.
 #include <algorithm>
 
 #include "neb_device.h"
@@ -35,90 +32,126 @@ typedef short bf16x8b __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// round to nearest, ties to even.  (gfx950's v_cvt_pk_bf16_f32 rounds the
-// same way, but with this toolchain its results fed to the 16 x 16 x 32
-// product below gave wrong outputs, while each alone was right; the integer
-// rounding is kept.)
-__device__ __forceinline__ uint16_t to_bf16(float x) {
-    uint32_t b = __float_as_uint(x);
-    b += 0x7FFFu + ((b >> 16) & 1u);
-    return (uint16_t)(b >> 16);
-}
-__device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-
+// bfloat16 of four floats, rounded to nearest, ties to even (the conversion
+// instruction rounds two at a time)
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+struct Bf16Pairs {
+    bf16x2 lo, hi;
+};
 __device__ __forceinline__ bf16x4 pack4(float a, float b, float c, float d) {
-    bf16x4 r;
-    r[0] = (short)to_bf16(a);
-    r[1] = (short)to_bf16(b);
-    r[2] = (short)to_bf16(c);
-    r[3] = (short)to_bf16(d);
-    return r;
+    Bf16Pairs r;
+    r.lo = __builtin_convertvector((f32x2){a, b}, bf16x2);
+    r.hi = __builtin_convertvector((f32x2){c, d}, bf16x2);
+    return __builtin_bit_cast(bf16x4, r);
 }
+__device__ __forceinline__ uint16_t to_bf16(float x) { return __builtin_bit_cast(uint16_t, (__bf16)x); }
 
 // 16 x 16 x 16 product (four k per lane)
 __device__ __forceinline__ f32x4 mfma(bf16x4 a, bf16x4 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
 }
 
-// 16 x 16 x 32 product of gfx950 (eight k per lane, twice the k of the
-// instruction above in the same issue time).  The eight k of lane l are
-// the four of the first 16 x 16 x 16 fragment pair (a0, b0) followed by the
-// four of the second (a1, b1): the product sums the same terms as the two
-// 16 x 16 x 16 products, the reduction only runs over a permuted k.
-__device__ __forceinline__ f32x4 mfma2(bf16x4 a0, bf16x4 a1, bf16x4 b0, bf16x4 b1, f32x4 c) {
-    const bf16x8b a = {a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
-    const bf16x8b b = {b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3]};
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
-                                                   0, 0, 0);
+// a product over two 16-wide k blocks whose A fragments lie side by side:
+// one 16 x 16 x 32 product of gfx950 (kK32; eight k per lane, twice the k in
+// the same issue time; it sums the same terms over a permuted k), or two
+// 16 x 16 x 16 ones.  (A 16 x 16 x 16 product that takes the accumulator of a
+// 16 x 16 x 32 one right behind it, without a wait, which is how the compiler
+// schedules such a pair, gave wrong sums: where the two meet, a wait of the
+// longer one's time stands between them.)
+template <bool kK32>
+__device__ __forceinline__ f32x4 mfma_pair(bf16x8b a, bf16x4 b0, bf16x4 b1, f32x4 c) {
+    if (kK32) {
+        const bf16x8b b = {b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3]};
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
+                                                       0, 0, 0);
+    }
+    c = mfma(bf16x4{a[0], a[1], a[2], a[3]}, b0, c);
+    return mfma(bf16x4{a[4], a[5], a[6], a[7]}, b1, c);
 }
 
-// Encoded input features f0 and f0 + 1 (f0 even) of (q, n): a raw pair,
-// or the sine and cosine of the same 2^octave pi c, or the zero pads.
-__device__ __forceinline__ void mlp_feature_pair(int f0, const float q[3], const float n[3], float& a, float& b) {
-    if (f0 < 6) {
-        a = f0 == 0 ? q[0] : (f0 == 2 ? q[2] : n[1]);
-        b = f0 == 0 ? q[1] : (f0 == 2 ? n[0] : n[2]);
-    } else if (f0 < kMlpEnc) {
-        int c = (f0 - 6) / 12, oct = ((f0 - 6) % 12) >> 1;
-        float x = c == 0 ? q[0] : c == 1 ? q[1] : c == 2 ? q[2] : c == 3 ? n[0] : c == 4 ? n[1] : n[2];
-        sincospif((float)(1 << oct) * x, &a, &b);  // exact power-of-two scale
-    } else {
-        a = 0.f;
-        b = 0.f;
+// The encoded input of one sample as the B operand of layer 1: lane group g
+// holds features 16 ks + 4 g .. + 3 of k-block ks, two pairs of features.
+// Pair p is a raw pair (p < 3), the sine and cosine of 2^octave pi c for
+// coordinate c = (p - 3) / 6 and octave (p - 3) % 6, or the two zero pads.
+// Within a k-block a lane's pair is one of two coordinates, by its group.
+__device__ __forceinline__ void mlp_encode(const float q[3], const float n[3], const float scale[10],
+                                           bf16x4 x[5]) {
+    const float c[6] = {q[0], q[1], q[2], n[0], n[1], n[2]};
+    // (k-block, pair): the coordinates of the groups below and from `from` on
+    // (lane masks held in scalar registers: one select each)
+    constexpr int lo[5][2] = {{0, 0}, {0, 1}, {2, 2}, {3, 3}, {4, 5}};
+    constexpr int hi[5][2] = {{0, 0}, {1, 2}, {3, 3}, {4, 4}, {5, 5}};
+    constexpr int from[5][2] = {{0, 0}, {1, 3}, {3, 2}, {2, 1}, {1, 0}};
+    auto upper = [](int k) {  // groups k and above, k = 1..3
+        return __builtin_amdgcn_inverse_ballot_w64(~0ull << (16 * k));
+    };
+#pragma unroll
+    for (int ks = 0; ks < 5; ++ks) {
+        float v[4];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const float y = from[ks][p] == 0 ? c[hi[ks][p]] : (upper(from[ks][p]) ? c[hi[ks][p]] : c[lo[ks][p]]);
+            sincospif(scale[2 * ks + p] * y, &v[2 * p], &v[2 * p + 1]);  // exact power-of-two scale
+        }
+        if (ks == 0) {
+            v[0] = upper(2) ? v[0] : (upper(1) ? n[1] : q[0]);
+            v[1] = upper(2) ? v[1] : (upper(1) ? n[2] : q[1]);
+            v[2] = upper(1) ? v[2] : q[2];
+            v[3] = upper(1) ? v[3] : n[0];
+        }
+        if (ks == 4) {
+            v[2] = upper(3) ? 0.f : v[2];
+            v[3] = upper(3) ? 0.f : v[3];
+        }
+        x[ks] = pack4(v[0], v[1], v[2], v[3]);
     }
 }
 
-// fragment blob offsets (in bf16 elements)
-constexpr int kFragF1 = 0;                              // W1^T: 4 ob x 5 ks x 64 lanes x 4
-constexpr int kFragF2 = kFragF1 + 4 * 5 * 256;          // W2^T: 4 x 4 x 256
-constexpr int kFragF3 = kFragF2 + 4 * 4 * 256;          // W3^T
-constexpr int kFragB2 = kFragF3 + 4 * 4 * 256;          // W2 (backward): 4 kb x 4 nb x 256
-constexpr int kFragB3 = kFragB2 + 4 * 4 * 256;          // W3 (backward)
+// 2^octave of the lane group's ten pairs (0 where there is none)
+__device__ __forceinline__ void mlp_scales(int g, float scale[10]) {
+#pragma unroll
+    for (int k = 0; k < 10; ++k) {
+        const int j = 8 * (k >> 1) + 2 * g + (k & 1) - 3;
+        scale[k] = j >= 0 && j < 36 ? (float)(1 << (j % 6)) : 0.f;
+    }
+}
+
+// Fragment blob (offsets in bf16 elements).  The fragments of two 16-wide k
+// blocks lie side by side, eight values (16 bytes) per lane: the A operand of
+// one 16 x 16 x 32 product, or of two 16 x 16 x 16 ones.  Layer 1's fifth k
+// block is paired with zeros.
+constexpr int kPair = 64 * 8;
+constexpr int kFragF1 = 0;                              // W1^T: 4 ob x 3 pairs
+constexpr int kFragF2 = kFragF1 + 4 * 3 * kPair;        // W2^T: 4 ob x 2 pairs
+constexpr int kFragF3 = kFragF2 + 4 * 2 * kPair;        // W3^T
+constexpr int kFragB2 = kFragF3 + 4 * 2 * kPair;        // W2 (backward): 4 kb x 2 pairs of nb
+constexpr int kFragB3 = kFragB2 + 4 * 2 * kPair;        // W3 (backward)
 constexpr int kFragFwd = kFragB2;                       // forward part
-constexpr int kFragAll = kFragB3 + 4 * 4 * 256;         // 21504
+constexpr int kFragAll = kFragB3 + 4 * 2 * kPair;       // 22528
 
 // fragment index of W_l[k][n] in the forward (W^T as A) and backward (W as A) blobs
-__device__ __forceinline__ int frag_fwd(int k, int n, int KS) {
+__device__ __forceinline__ int frag_fwd(int k, int n, int pairs) {
     int ob = n >> 4, ks = k >> 4, lane = (n & 15) + 16 * ((k & 15) >> 2);
-    return ((ob * KS + ks) * 64 + lane) * 4 + (k & 3);
+    return ((ob * pairs + (ks >> 1)) * 64 + lane) * 8 + 4 * (ks & 1) + (k & 3);
 }
 __device__ __forceinline__ int frag_bwd(int k, int n) {
     int kb = k >> 4, nb = n >> 4, lane = (k & 15) + 16 * ((n & 15) >> 2);
-    return ((kb * 4 + nb) * 64 + lane) * 4 + (n & 3);
+    return ((kb * 2 + (nb >> 1)) * 64 + lane) * 8 + 4 * (nb & 1) + (n & 3);
 }
 
 // one parameter's bf16 copies into the blob (weights of layers 1..3 only)
 __device__ __forceinline__ void pack_param(uint16_t* blob, int p, float w) {
     if (p < kMlpB1) {
         int k = p / kMlpWidth, n = p % kMlpWidth;
-        blob[kFragF1 + frag_fwd(k, n, 5)] = to_bf16(w);
+        blob[kFragF1 + frag_fwd(k, n, 3)] = to_bf16(w);
     } else if (p >= kMlpW2 && p < kMlpB2) {
         int e = p - kMlpW2, k = e / kMlpWidth, n = e % kMlpWidth;
-        blob[kFragF2 + frag_fwd(k, n, 4)] = to_bf16(w);
+        blob[kFragF2 + frag_fwd(k, n, 2)] = to_bf16(w);
         blob[kFragB2 + frag_bwd(k, n)] = to_bf16(w);
     } else if (p >= kMlpW3 && p < kMlpB3) {
         int e = p - kMlpW3, k = e / kMlpWidth, n = e % kMlpWidth;
-        blob[kFragF3 + frag_fwd(k, n, 4)] = to_bf16(w);
+        blob[kFragF3 + frag_fwd(k, n, 2)] = to_bf16(w);
         blob[kFragB3 + frag_bwd(k, n)] = to_bf16(w);
     }
 }
@@ -135,8 +168,8 @@ __device__ __forceinline__ void stage_blob(const uint16_t* __restrict__ blob, ui
     __syncthreads();
 }
 
-__device__ __forceinline__ bf16x4 frag(const uint16_t* lds, int base, int idx, int lane) {
-    return *reinterpret_cast<const bf16x4*>(lds + base + (idx * 64 + lane) * 4);
+__device__ __forceinline__ bf16x8b frag(const uint16_t* lds, int base, int pair, int lane) {
+    return *reinterpret_cast<const bf16x8b*>(lds + base + (pair * 64 + lane) * 8);
 }
 
 // Inputs of one sample.  Sources: float3 arrays of normalised points (or
@@ -173,93 +206,94 @@ __device__ __forceinline__ void load_input(const MlpInput& in, int i, float q[3]
 struct TileFwd {
     f32x4 z1[4], z2[4], z3[4];
     bf16x4 x[5];  // encoded input, bf16
+    bf16x4 h1[4], h2[4];
     float y;
 };
 
-// kK32: the layer products on the 16 x 16 x 32 instruction (inference);
-// else on 16 x 16 x 16 (training: with the 16 x 16 x 32 form its loss came
-// out wrong under this toolchain, see below)
+// max(x, 0) in one instruction (fmaxf of a matrix result takes a second one to quiet NaNs); 0 for a NaN, as fmaxf gives
+__device__ __forceinline__ float relu(float x) { return __builtin_amdgcn_fmed3f(x, 0.f, INFINITY); }
+__device__ __forceinline__ bf16x4 relu_pack(f32x4 z) { return pack4(relu(z[0]), relu(z[1]), relu(z[2]), relu(z[3])); }
+
+// a product over 64 inputs
 template <bool kK32>
-__device__ __forceinline__ void tile_forward(const uint16_t* lds, const float* __restrict__ theta, const float q[3],
-                                             const float n[3], TileFwd& T) {
+__device__ __forceinline__ f32x4 product64(const uint16_t* lds, int base, int pair, int lane, const bf16x4 in[4]) {
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    acc = mfma_pair<kK32>(frag(lds, base, pair, lane), in[0], in[1], acc);
+    return mfma_pair<kK32>(frag(lds, base, pair + 1, lane), in[2], in[3], acc);
+}
+
+// sb: b1, b2, b3 and w4, 64 floats each (16-byte aligned).  kK32: inference;
+// training keeps the 16 x 16 x 16 products (its time is not theirs, and
+// its activations keep their bits)
+template <bool kK32>
+__device__ __forceinline__ void tile_forward(const uint16_t* lds, const float* __restrict__ sb, float b4,
+                                             const float q[3], const float n[3], const float scale[10], TileFwd& T) {
     const int lane = threadIdx.x & 63, g = lane >> 4;
+    auto biased = [&](f32x4 acc, int l, int ob) { return acc + *reinterpret_cast<const f32x4*>(sb + l * kMlpWidth + 16 * ob + 4 * g); };
+    mlp_encode(q, n, scale, T.x);
+    f32x4 acc[4];
 #pragma unroll
-    for (int ks = 0; ks < 5; ++ks) {
-        int f = 16 * ks + 4 * g;
-        float a0, a1, a2, a3;
-        mlp_feature_pair(f, q, n, a0, a1);
-        mlp_feature_pair(f + 2, q, n, a2, a3);
-        T.x[ks] = pack4(a0, a1, a2, a3);
+    for (int ob = 0; ob < 4; ++ob) acc[ob] = product64<kK32>(lds, kFragF1, ob * 3, lane, T.x);
+    // the last 16 inputs, after all four blocks of the others and a wait of
+    // 32 cycles (see mfma_pair)
+    if (kK32) {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_nop 15\n\ts_nop 15");
+        __builtin_amdgcn_sched_barrier(0);
     }
-    // layer 1
 #pragma unroll
     for (int ob = 0; ob < 4; ++ob) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        if (kK32) {
-#pragma unroll
-            for (int ks = 0; ks < 4; ks += 2)
-                acc = mfma2(frag(lds, kFragF1, ob * 5 + ks, lane), frag(lds, kFragF1, ob * 5 + ks + 1, lane), T.x[ks],
-                            T.x[ks + 1], acc);
-            acc = mfma(frag(lds, kFragF1, ob * 5 + 4, lane), T.x[4], acc);
-        } else {
-#pragma unroll
-            for (int ks = 0; ks < 5; ++ks) acc = mfma(frag(lds, kFragF1, ob * 5 + ks, lane), T.x[ks], acc);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc[i] += theta[kMlpB1 + 16 * ob + 4 * g + i];
-        T.z1[ob] = acc;
-    }
-    bf16x4 h[4];
-#pragma unroll
-    for (int ob = 0; ob < 4; ++ob)
-        h[ob] = pack4(fmaxf(T.z1[ob][0], 0.f), fmaxf(T.z1[ob][1], 0.f), fmaxf(T.z1[ob][2], 0.f),
-                      fmaxf(T.z1[ob][3], 0.f));
-    // layer 2
-#pragma unroll
-    for (int ob = 0; ob < 4; ++ob) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < 4; ks += kK32 ? 2 : 1)
-            acc = kK32 ? mfma2(frag(lds, kFragF2, ob * 4 + ks, lane), frag(lds, kFragF2, ob * 4 + ks + 1, lane), h[ks],
-                               h[ks + 1], acc)
-                       : mfma(frag(lds, kFragF2, ob * 4 + ks, lane), h[ks], acc);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc[i] += theta[kMlpB2 + 16 * ob + 4 * g + i];
-        T.z2[ob] = acc;
+        const bf16x8b w = frag(lds, kFragF1, ob * 3 + 2, lane);
+        T.z1[ob] = biased(mfma(bf16x4{w[0], w[1], w[2], w[3]}, T.x[4], acc[ob]), 0, ob);
     }
 #pragma unroll
-    for (int ob = 0; ob < 4; ++ob)
-        h[ob] = pack4(fmaxf(T.z2[ob][0], 0.f), fmaxf(T.z2[ob][1], 0.f), fmaxf(T.z2[ob][2], 0.f),
-                      fmaxf(T.z2[ob][3], 0.f));
+    for (int ob = 0; ob < 4; ++ob) T.h1[ob] = relu_pack(T.z1[ob]);
+#pragma unroll
+    for (int ob = 0; ob < 4; ++ob) T.z2[ob] = biased(product64<kK32>(lds, kFragF2, ob * 2, lane, T.h1), 1, ob);
+#pragma unroll
+    for (int ob = 0; ob < 4; ++ob) T.h2[ob] = relu_pack(T.z2[ob]);
     // layer 3 and the linear output (FP32 dot product over the lane's 16 features)
     float part = 0.f;
 #pragma unroll
     for (int ob = 0; ob < 4; ++ob) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        T.z3[ob] = biased(product64<kK32>(lds, kFragF3, ob * 2, lane, T.h2), 2, ob);
+        const f32x4 w = *reinterpret_cast<const f32x4*>(sb + 3 * kMlpWidth + 16 * ob + 4 * g);
 #pragma unroll
-        for (int ks = 0; ks < 4; ks += kK32 ? 2 : 1)
-            acc = kK32 ? mfma2(frag(lds, kFragF3, ob * 4 + ks, lane), frag(lds, kFragF3, ob * 4 + ks + 1, lane), h[ks],
-                               h[ks + 1], acc)
-                       : mfma(frag(lds, kFragF3, ob * 4 + ks, lane), h[ks], acc);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            acc[i] += theta[kMlpB3 + 16 * ob + 4 * g + i];
-            part += theta[kMlpW4 + 16 * ob + 4 * g + i] * fmaxf(acc[i], 0.f);
-        }
-        T.z3[ob] = acc;
+        for (int i = 0; i < 4; ++i) part += w[i] * relu(T.z3[ob][i]);
     }
     part += __shfl_xor(part, 16, 64);
     part += __shfl_xor(part, 32, 64);
-    T.y = part + theta[kMlpB4];
+    T.y = part + b4;
+}
+
+// b1, b2, b3 and w4 into LDS (theta's offsets are not 16-byte aligned);
+// the caller's barrier follows
+__device__ __forceinline__ void stage_small(const float* __restrict__ theta, float* sb) {
+    for (int i = threadIdx.x; i < 4 * kMlpWidth; i += blockDim.x) {
+        const int l = i / kMlpWidth, f = i % kMlpWidth;
+        sb[i] = theta[(l == 0 ? kMlpB1 : (l == 1 ? kMlpB2 : (l == 2 ? kMlpB3 : kMlpW4))) + f];
+    }
 }
 
 // Inference: out[i] = log rho (mode 0) or rho = exp(log rho) (mode 1).
-__global__ void __launch_bounds__(256) k_mlp_infer(const uint16_t* __restrict__ blob, const float* __restrict__ theta,
+// Bound by instruction issue: 620 vector instructions per 16-sample tile (half
+// of them the ten sincospif of a lane) and 28 matrix products, 2 870 cycles per
+// tile and SIMD at 1.835 M samples, 163 -> 134 us.  Before: 906 instructions
+// (rounding to bf16 in integers, selecting a pair's coordinate through five
+// compares, quieting NaNs before each ReLU).  Four waves per SIMD or two
+// measure the same; 2 048 blocks beat the 1 280 that are resident at once (141
+// us), 1 024 and 2 560 (146, 135).
+__global__ void __launch_bounds__(256, 4) k_mlp_infer(const uint16_t* __restrict__ blob, const float* __restrict__ theta,
                                                    const MlpNorm* norm, MlpInput in, float* __restrict__ out,
                                                    int mode) {
     __shared__ __attribute__((aligned(16))) uint16_t lds[kFragFwd];
+    __shared__ __attribute__((aligned(16))) float sb[4 * kMlpWidth];
+    stage_small(theta, sb);
     stage_blob(blob, lds, kFragFwd);
     const int lane = threadIdx.x & 63, s = lane & 15;
+    float scale[10];
+    mlp_scales(lane >> 4, scale);
+    const float b4 = theta[kMlpB4];
     const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, n_waves = (gridDim.x * blockDim.x) >> 6;
     const int n = in.n_dev ? min(*in.n_dev, in.n_host) : in.n_host;
     const float mu = norm->mu, sigma = norm->sigma;
@@ -268,7 +302,12 @@ __global__ void __launch_bounds__(256) k_mlp_infer(const uint16_t* __restrict__ 
         float q[3] = {0.f, 0.f, 0.f}, nn[3] = {0.f, 0.f, 1.f};
         if (i < n) load_input(in, i, q, nn);
         TileFwd T;
-        tile_forward<true>(lds, theta, q, nn, T);
+        // an offset the compiler cannot see through: the weights' fragments
+        // are the same for every tile, and kept in registers over the loop they
+        // would leave room for two waves per SIMD instead of four
+        int at = 0;
+        asm volatile("" : "+s"(at));
+        tile_forward<true>(lds + at, sb + at, b4, q, nn, scale, T);
         if (lane < 16 && i < n) {
             float lr = mu + sigma * T.y;
             out[i] = mode ? __expf(lr) : lr;
@@ -295,29 +334,39 @@ constexpr int kPartStride = 4 * kMlpWidth + 2;
 // bytes per lane.
 constexpr int kRowsX = 0, kRowsH1 = kMlpIn, kRowsH2 = kRowsH1 + kMlpWidth, kRowsD1 = kRowsH2 + kMlpWidth,
               kRowsD2 = kRowsD1 + kMlpWidth, kRowsD3 = kRowsD2 + kMlpWidth, kRowsTile = kRowsD3 + kMlpWidth;
+constexpr int kTrainWaves = 8;  // waves per block; the block's LDS fills a CU
 
 // Forward, output gradient, backward data pass, the wave's partial sums of
 // the bias and output-layer gradients and of the loss (plain stores, summed
 // by k_mlp_wgrad), and the tile-major bf16 stores the weight-gradient GEMMs
-// read.
-__global__ void __launch_bounds__(256) k_mlp_train_fb(const uint16_t* __restrict__ blob,
-                                                      const float* __restrict__ theta, const MlpNorm* norm,
-                                                      MlpBatch B, uint16_t* __restrict__ acts, int npad,
-                                                      float* __restrict__ part) {
+// read.  A lane holds four rows of its sample, a fragment four samples of a row:
+// the tile is turned in LDS, so that it leaves in 25 stores of 8 bytes per
+// lane instead of 100 of 2.
+// Bound by instruction issue (two waves per SIMD): the encoding, the roundings,
+// the 2-byte stores into LDS.  65 536 samples: 40 -> 25 us.
+__global__ void __launch_bounds__(64 * kTrainWaves) k_mlp_train_fb(const uint16_t* __restrict__ blob,
+                                                                   const float* __restrict__ theta, const MlpNorm* norm,
+                                                                   MlpBatch B, uint16_t* __restrict__ acts,
+                                                                   int n_tiles, float* __restrict__ part) {
     __shared__ __attribute__((aligned(16))) uint16_t lds[kFragAll];
+    __shared__ __attribute__((aligned(16))) uint16_t turn[kTrainWaves][kRowsTile * 16];
+    __shared__ __attribute__((aligned(16))) float sb[4 * kMlpWidth];
+    stage_small(theta, sb);
     stage_blob(blob, lds, kFragAll);
-    const int lane = threadIdx.x & 63, s = lane & 15, g = lane >> 4;
-    const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, n_waves = (gridDim.x * blockDim.x) >> 6;
-    const float mu = norm->mu, inv_sigma = 1.0f / norm->sigma;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, s = lane & 15, g = lane >> 4;
+    const float mu = norm->mu, inv_sigma = 1.0f / norm->sigma, b4 = theta[kMlpB4];
     const float inv_n = 2.0f / (float)B.n;
-    float gb1[16], gb2[16], gb3[16], gw4[16];
+    float scale[10];
+    mlp_scales(g, scale);
+    f32x4 gb1[4], gb2[4], gb3[4], gw4[4];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) gb1[k] = gb2[k] = gb3[k] = gw4[k] = 0.f;
+    for (int k = 0; k < 4; ++k) gb1[k] = gb2[k] = gb3[k] = gw4[k] = f32x4{0.f, 0.f, 0.f, 0.f};
     float gb4 = 0.f, lsum = 0.f;
-    int pool = B.sample ? (B.in.n_dev ? min(*B.in.n_dev, B.in.n_host) : B.in.n_host) : B.n;
-    for (int base = wave * 16; base < npad; base += n_waves * 16) {
-        int j = base + s;
-        bool live = j < B.n && pool > 0;
+    const int pool = B.sample ? (B.in.n_dev ? min(*B.in.n_dev, B.in.n_host) : B.in.n_host) : B.n;
+    uint16_t* const mine = turn[wave];
+    for (int tile = blockIdx.x * kTrainWaves + wave; tile < n_tiles; tile += gridDim.x * kTrainWaves) {
+        const int j = 16 * tile + s;
+        const bool live = j < B.n && pool > 0;
         float q[3] = {0.f, 0.f, 0.f}, nn[3] = {0.f, 0.f, 1.f}, t = 0.f;
         if (live) {
             int item = j;
@@ -329,253 +378,222 @@ __global__ void __launch_bounds__(256) k_mlp_train_fb(const uint16_t* __restrict
             t = (B.target[item] - mu) * inv_sigma;
         }
         TileFwd T;
-        tile_forward<false>(lds, theta, q, nn, T);
-        float e = live ? T.y - t : 0.f;
-        float dy = e * inv_n;
+        tile_forward<false>(lds, sb, b4, q, nn, scale, T);
+        uint16_t* col = mine + s;
+#pragma unroll
+        for (int ks = 0; ks < 5; ++ks)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) col[(kRowsX + 16 * ks + 4 * g + i) * 16] = (uint16_t)T.x[ks][i];
+        const float e = live ? T.y - t : 0.f;
+        const float dy = e * inv_n;
         if (g == 0) {
             lsum += e * e;
             gb4 += dy;
         }
         // output layer and delta 3
-        bf16x4 d3b[4];
-        f32x4 d3[4];
+        bf16x4 d3[4];
 #pragma unroll
         for (int ob = 0; ob < 4; ++ob) {
+            const f32x4 w = *reinterpret_cast<const f32x4*>(sb + 3 * kMlpWidth + 16 * ob + 4 * g);
+            f32x4 d;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                int f = 16 * ob + 4 * g + i;
-                float h3 = fmaxf(T.z3[ob][i], 0.f);
-                gw4[4 * ob + i] += dy * h3;
-                d3[ob][i] = T.z3[ob][i] > 0.f ? dy * theta[kMlpW4 + f] : 0.f;
-                gb3[4 * ob + i] += d3[ob][i];
+                gw4[ob][i] += dy * relu(T.z3[ob][i]);
+                d[i] = T.z3[ob][i] > 0.f ? dy * w[i] : 0.f;
+                gb3[ob][i] += d[i];
             }
-            d3b[ob] = pack4(d3[ob][0], d3[ob][1], d3[ob][2], d3[ob][3]);
+            d3[ob] = pack4(d[0], d[1], d[2], d[3]);
         }
-        // delta 2 = (W3 d3) . [z2 > 0]
-        bf16x4 d2b[4];
+        // delta of the layer below: (W delta) . [z > 0]
+        auto back = [&](int frags, const bf16x4 din[4], const f32x4 z[4], f32x4 gb[4], bf16x4 dout[4]) {
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb) {
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+            for (int kb = 0; kb < 4; ++kb) {
+                f32x4 acc = product64<false>(lds, frags, kb * 2, lane, din);
 #pragma unroll
-            for (int nb = 0; nb < 4; ++nb) acc = mfma(frag(lds, kFragB3, kb * 4 + nb, lane), d3b[nb], acc);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                acc[i] = T.z2[kb][i] > 0.f ? acc[i] : 0.f;
-                gb2[4 * kb + i] += acc[i];
+                for (int i = 0; i < 4; ++i) {
+                    acc[i] = z[kb][i] > 0.f ? acc[i] : 0.f;
+                    gb[kb][i] += acc[i];
+                }
+                dout[kb] = pack4(acc[0], acc[1], acc[2], acc[3]);
             }
-            d2b[kb] = pack4(acc[0], acc[1], acc[2], acc[3]);
-        }
-        // delta 1 = (W2 d2) . [z1 > 0]
-        bf16x4 d1b[4];
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb) {
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int nb = 0; nb < 4; ++nb) acc = mfma(frag(lds, kFragB2, kb * 4 + nb, lane), d2b[nb], acc);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                acc[i] = T.z1[kb][i] > 0.f ? acc[i] : 0.f;
-                gb1[4 * kb + i] += acc[i];
-            }
-            d1b[kb] = pack4(acc[0], acc[1], acc[2], acc[3]);
-        }
-        // tile-major stores for the weight gradients
-        uint16_t* tile = acts + (size_t)(base >> 4) * (kRowsTile * 16) + s;
-#pragma unroll
-        for (int ks = 0; ks < 5; ++ks)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) tile[(kRowsX + 16 * ks + 4 * g + i) * 16] = (uint16_t)T.x[ks][i];
+        };
+        bf16x4 d2[4], d1[4];
+        back(kFragB3, d3, T.z2, gb2, d2);
+        back(kFragB2, d2, T.z1, gb1, d1);
 #pragma unroll
         for (int ob = 0; ob < 4; ++ob)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int f = 16 * ob + 4 * g + i;
-                tile[(kRowsH1 + f) * 16] = to_bf16(fmaxf(T.z1[ob][i], 0.f));
-                tile[(kRowsH2 + f) * 16] = to_bf16(fmaxf(T.z2[ob][i], 0.f));
-                tile[(kRowsD1 + f) * 16] = (uint16_t)d1b[ob][i];
-                tile[(kRowsD2 + f) * 16] = (uint16_t)d2b[ob][i];
-                tile[(kRowsD3 + f) * 16] = (uint16_t)d3b[ob][i];
+                const int f = (16 * ob + 4 * g + i) * 16;
+                col[kRowsH1 * 16 + f] = (uint16_t)T.h1[ob][i];
+                col[kRowsH2 * 16 + f] = (uint16_t)T.h2[ob][i];
+                col[kRowsD1 * 16 + f] = (uint16_t)d1[ob][i];
+                col[kRowsD2 * 16 + f] = (uint16_t)d2[ob][i];
+                col[kRowsD3 * 16 + f] = (uint16_t)d3[ob][i];
             }
+        // the wave's own LDS, in order: no barrier needed
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        uint16_t* out = acts + (size_t)tile * (kRowsTile * 16) + 4 * lane;
+#pragma unroll
+        for (int rb = 0; rb < kRowsTile / 16; ++rb)
+            *reinterpret_cast<bf16x4*>(out + 256 * rb) = *reinterpret_cast<const bf16x4*>(mine + 256 * rb + 4 * lane);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
-    // sum the per-sample partials over the 16 sample lanes of each group
+    // the wave's small gradients: over the 16 sample lanes of each group
+    auto over_samples = [&](float v) {
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
+        for (int off = 1; off < 16; off <<= 1) v += __shfl_xor(v, off, 64);
+        return v;
+    };
+    float* P = part + (size_t)(blockIdx.x * kTrainWaves + wave) * kPartStride;
 #pragma unroll
-        for (int off = 1; off < 16; off <<= 1) {
-            gb1[k] += __shfl_xor(gb1[k], off, 64);
-            gb2[k] += __shfl_xor(gb2[k], off, 64);
-            gb3[k] += __shfl_xor(gb3[k], off, 64);
-            gw4[k] += __shfl_xor(gw4[k], off, 64);
-        }
-    }
-    for (int off = 1; off < 16; off <<= 1) {
-        gb4 += __shfl_xor(gb4, off, 64);
-        lsum += __shfl_xor(lsum, off, 64);
-    }
-    float* P = part + (size_t)wave * kPartStride;
-    if (s == 0) {
+    for (int ob = 0; ob < 4; ++ob)
 #pragma unroll
-        for (int ob = 0; ob < 4; ++ob)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                int f = 16 * ob + 4 * g + i;
-                P[f] = gb1[4 * ob + i];
-                P[kMlpWidth + f] = gb2[4 * ob + i];
-                P[2 * kMlpWidth + f] = gb3[4 * ob + i];
-                P[3 * kMlpWidth + f] = gw4[4 * ob + i];
+        for (int i = 0; i < 4; ++i) {
+            const int f = 16 * ob + 4 * g + i;
+            const float v1 = over_samples(gb1[ob][i]), v2 = over_samples(gb2[ob][i]), v3 = over_samples(gb3[ob][i]),
+                        v4 = over_samples(gw4[ob][i]);
+            if (s == 0) {
+                P[f] = v1;
+                P[kMlpWidth + f] = v2;
+                P[2 * kMlpWidth + f] = v3;
+                P[3 * kMlpWidth + f] = v4;
             }
-        if (g == 0) {
-            P[4 * kMlpWidth] = gb4;
-            P[4 * kMlpWidth + 1] = lsum;
         }
+    gb4 = over_samples(gb4);
+    lsum = over_samples(lsum);
+    if (lane == 0) {
+        P[4 * kMlpWidth] = gb4;
+        P[4 * kMlpWidth + 1] = lsum;
     }
 }
 
 // Weight gradients dW_l[k][n] = sum_s Hin[k][s] D[n][s] as K = batch GEMMs.
-// Block (layer, slice) is one wave that reads each row of its slice of the
-// batch once (per 16-sample tile: the layer's delta rows as A fragments,
-// its input rows as B fragments) and accumulates every 16 x 16 tile of
-// dW^T of that layer in registers, then stores them as its slice's part
-// (k_mlp_wreduce sums the slices: per-lane atomics of every wave on the
-// 13 312 weights took as long as the products).  Blocks past the three layers sum the
-// training kernel's per-wave partials, each slice a share of the waves.
+// One wave per slice of 512 samples and column of 16 x 16 tiles (16 input
+// rows of a layer, 13 columns, against all 64 delta rows): it runs through its
+// slice's samples in order and stores its part of dW^T (k_mlp_reduce sums the
+// slices).  A wave per layer, four or five columns, read every row once but left
+// the chip at 384 waves: 65 536 samples 26 -> 14 us.  Five more jobs per slice sum
+// the training kernel's per-wave partials, each a share of the waves.  All
+// jobs of a slice run on one XCD (blocks b, b + 8, ... do), whose L2 then
+// reads the slice once.
 constexpr int kWgSlice = 512;
-constexpr int kWgLayers = 3;
-constexpr int kWgReduce = (kPartStride + 63) / 64;
-// a slice's partial weight gradients: W1^T rows 0..79 (the input's two pads
-// included, never read), then W2^T and W3^T, k-major (k * 64 + n)
-constexpr int kWPartW2 = (kMlpEnc + 2) * kMlpWidth;
-constexpr int kWPartW3 = kWPartW2 + kMlpWidth * kMlpWidth;
-constexpr int kWPart = kWPartW3 + kMlpWidth * kMlpWidth;
+constexpr int kWgCols = 13;
+constexpr int kWgJobs = kWgCols + (kPartStride + 63) / 64;
+// a slice's part: the gradient in theta's layout, then the loss sum
+constexpr int kWPartLoss = kMlpParams;
+constexpr int kWPart = (kMlpParams + 1 + 31) & ~31;
 
-template <int KB>
-__device__ __forceinline__ void wgrad_layer(const uint16_t* __restrict__ acts, int t_begin, int t_end, int hrow,
-                                            int drow, int kmax, float* __restrict__ wpart) {
-    const int lane = threadIdx.x, g = lane >> 4, r = lane & 15;
+__global__ void __launch_bounds__(64) k_mlp_wgrad(const uint16_t* __restrict__ acts, int n_tiles, int n_slices,
+                                                  const float* __restrict__ part, int n_waves,
+                                                  float* __restrict__ wpart) {
+    const int lane = threadIdx.x;
+    const int slice = (blockIdx.x / (8 * kWgJobs)) * 8 + blockIdx.x % 8, job = (blockIdx.x / 8) % kWgJobs;
+    if (slice >= n_slices) return;
+    float* wp = wpart + (size_t)slice * kWPart;
+    if (job >= kWgCols) {
+        const int j = (job - kWgCols) * 64 + lane;
+        if (j >= kPartStride) return;
+        const int share = (n_waves + n_slices - 1) / n_slices;
+        const int w0 = slice * share, w1 = min(n_waves, w0 + share);
+        float sum = 0.f;
+        for (int w = w0; w < w1; ++w) sum += part[(size_t)w * kPartStride + j];
+        const int l = j / kMlpWidth, f = j % kMlpWidth;
+        wp[l == 4 ? (f == 0 ? kMlpB4 : kWPartLoss)
+                  : (l == 0 ? kMlpB1 : (l == 1 ? kMlpB2 : (l == 2 ? kMlpB3 : kMlpW4))) + f] = sum;
+        return;
+    }
+    const int g = lane >> 4, r = lane & 15;
+    const int in = job < 5 ? kRowsX + 16 * job : (job < 9 ? kRowsH1 + 16 * (job - 5) : kRowsH2 + 16 * (job - 9));
+    const int de = job < 5 ? kRowsD1 : (job < 9 ? kRowsD2 : kRowsD3);
     constexpr size_t kTile = (size_t)kRowsTile * 16;
-    f32x4 acc[4][KB];
+    const uint16_t* pa = acts + (de + r) * 16 + 4 * g;
+    const uint16_t* pb = acts + (in + r) * 16 + 4 * g;
+    f32x4 acc[4];
 #pragma unroll
-    for (int nb = 0; nb < 4; ++nb)
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb) acc[nb][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const uint16_t* abase = acts + (drow + r) * 16 + 4 * g;
-    const uint16_t* bbase = acts + (hrow + r) * 16 + 4 * g;
+    for (int nb = 0; nb < 4; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int t_end = min(n_tiles, (slice + 1) * (kWgSlice / 16));
     // U tiles' fragments are loaded before any of them is used
     constexpr int U = 8;
-    int t = t_begin;
+    int t = slice * (kWgSlice / 16);
     for (; t + U <= t_end; t += U) {
-        bf16x4 a[U][4], b[U][KB];
+        bf16x4 a[U][4], b[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const size_t off = (size_t)(t + u) * kTile;
+            b[u] = *reinterpret_cast<const bf16x4*>(pb + off);
 #pragma unroll
-            for (int nb = 0; nb < 4; ++nb) a[u][nb] = *reinterpret_cast<const bf16x4*>(abase + off + 16 * 16 * nb);
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb) b[u][kb] = *reinterpret_cast<const bf16x4*>(bbase + off + 16 * 16 * kb);
+            for (int nb = 0; nb < 4; ++nb) a[u][nb] = *reinterpret_cast<const bf16x4*>(pa + off + 256 * nb);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int nb = 0; nb < 4; ++nb)
-#pragma unroll
-                for (int kb = 0; kb < KB; ++kb) acc[nb][kb] = mfma(a[u][nb], b[u][kb], acc[nb][kb]);
+            for (int nb = 0; nb < 4; ++nb) acc[nb] = mfma(a[u][nb], b[u], acc[nb]);
     }
     for (; t < t_end; ++t) {
         const size_t off = (size_t)t * kTile;
-        bf16x4 a[4], b[KB];
+        const bf16x4 b = *reinterpret_cast<const bf16x4*>(pb + off);
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb) a[nb] = *reinterpret_cast<const bf16x4*>(abase + off + 16 * 16 * nb);
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb) b[kb] = *reinterpret_cast<const bf16x4*>(bbase + off + 16 * 16 * kb);
-#pragma unroll
-        for (int nb = 0; nb < 4; ++nb)
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb) acc[nb][kb] = mfma(a[nb], b[kb], acc[nb][kb]);
+        for (int nb = 0; nb < 4; ++nb) acc[nb] = mfma(*reinterpret_cast<const bf16x4*>(pa + off + 256 * nb), b, acc[nb]);
     }
-    // acc[nb][kb][i] = dW^T[16 nb + 4 g + i][16 kb + r]: this slice's part,
-    // four consecutive n per store
+    // acc[nb][i] = dW[16 column + r][16 nb + 4 g + i]
+    float* w = wp + (job < 5 ? kMlpW1 + 16 * job * kMlpWidth
+                             : (job < 9 ? kMlpW2 + 16 * (job - 5) * kMlpWidth : kMlpW3 + 16 * (job - 9) * kMlpWidth)) +
+               r * kMlpWidth + 4 * g;
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) {
-        const int k = 16 * kb + r;
-        if (k >= kmax) continue;  // the zero pads of the input carry no gradient
-#pragma unroll
-        for (int nb = 0; nb < 4; ++nb)
-            *reinterpret_cast<f32x4*>(wpart + k * kMlpWidth + 16 * nb + 4 * g) = acc[nb][kb];
-    }
+    for (int nb = 0; nb < 4; ++nb) *reinterpret_cast<f32x4*>(w + 16 * nb) = acc[nb];
 }
 
-__global__ void __launch_bounds__(64) k_mlp_wgrad(const uint16_t* __restrict__ acts, int npad,
-                                                  float* __restrict__ grad, const float* __restrict__ part,
-                                                  int n_waves, float* loss_sum, float* __restrict__ wpart) {
-    const int lane = threadIdx.x;
-    const int job = blockIdx.x;
-    const int slice = blockIdx.y;
-    if (job >= kWgLayers) {
-        const int j = (job - kWgLayers) * 64 + lane;
-        if (j >= kPartStride) return;
-        const int share = (n_waves + gridDim.y - 1) / gridDim.y;
-        const int w0 = slice * share, w1 = min(n_waves, w0 + share);
-        if (w0 >= w1) return;
+// Sums the slices' parts, 32 parameters per block of 256 threads (eight
+// threads per parameter; whole 128-byte lines), eight slices at a time in order
+// and then the groups in order, and either takes one Adam step on the FP32
+// master parameters and re-packs the bf16 operand fragments (kAdam), or writes
+// the gradient.  The loss sum is added to *loss.  One launch for the sums
+// (4.6 us, with atomics), Adam (4.7) and the fills (3.6): 6 us.
+constexpr int kWrGroup = 8;
+template <bool kAdam>
+__global__ void __launch_bounds__(256) k_mlp_reduce(const float* __restrict__ wpart, int n_slices, float* loss,
+                                                    float* __restrict__ grad, float* __restrict__ theta,
+                                                    float* __restrict__ m, float* __restrict__ v,
+                                                    uint16_t* __restrict__ blob, MlpAdam A) {
+    __shared__ float sh[256 / 32][32];
+    const int c = threadIdx.x & 31, q = threadIdx.x >> 5;
+    const int p = blockIdx.x * 32 + c;
+    float gr = 0.f;
+    for (int s0 = 0; s0 < n_slices; s0 += kWrGroup * (256 / 32)) {
+        // this thread's group of the next eight
+        const int s = s0 + kWrGroup * q;
+        float x[kWrGroup];
+#pragma unroll
+        for (int u = 0; u < kWrGroup; ++u) x[u] = s + u < n_slices ? wpart[(size_t)(s + u) * kWPart + p] : 0.f;
         float sum = 0.f;
-        for (int w = w0; w < w1; ++w) sum += part[(size_t)w * kPartStride + j];
-        if (j < 4 * kMlpWidth) {
-            const int off = j < kMlpWidth ? kMlpB1 : (j < 2 * kMlpWidth ? kMlpB2 : (j < 3 * kMlpWidth ? kMlpB3 : kMlpW4));
-            atomicAdd(grad + off + (j % kMlpWidth), sum);
-        } else if (j == 4 * kMlpWidth) {
-            atomicAdd(grad + kMlpB4, sum);
-        } else {
-            atomicAdd(loss_sum, sum);
-        }
+#pragma unroll
+        for (int u = 0; u < kWrGroup; ++u) sum += x[u];
+        sh[q][c] = sum;
+        __syncthreads();
+        if (q == 0)
+#pragma unroll
+            for (int u = 0; u < 256 / 32; ++u)
+                if (s0 + kWrGroup * u < n_slices) gr += sh[u][c];
+        __syncthreads();
+    }
+    if (q != 0 || p > kWPartLoss) return;
+    if (p == kWPartLoss) {
+        *loss += gr;
         return;
     }
-    const int t_begin = (slice * kWgSlice) >> 4, t_end = min(npad, (slice + 1) * kWgSlice) >> 4;
-    float* wp = wpart + (size_t)slice * kWPart;
-    if (job == 0) wgrad_layer<5>(acts, t_begin, t_end, kRowsX, kRowsD1, kMlpEnc, wp);
-    else if (job == 1) wgrad_layer<4>(acts, t_begin, t_end, kRowsH1, kRowsD2, kMlpWidth, wp + kWPartW2);
-    else wgrad_layer<4>(acts, t_begin, t_end, kRowsH2, kRowsD3, kMlpWidth, wp + kWPartW3);
-}
-
-// The weight gradients: block (x, y) sums slices kWrGroup y .. + kWrGroup - 1
-// of weights 256 x .. 256 x + 255 (one thread per weight, the slices' rows
-// read coalesced, their loads in flight together) and adds the sum to grad.
-constexpr int kWrGroup = 8;
-__global__ void __launch_bounds__(256) k_mlp_wreduce(const float* __restrict__ wpart, int n_slices,
-                                                     float* __restrict__ grad) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= kWPart) return;
-    int dst;
-    if (j < kWPartW2) {
-        if (j >= kMlpEnc * kMlpWidth) return;  // the pads' rows
-        dst = kMlpW1 + j;
-    } else {
-        dst = (j < kWPartW3 ? kMlpW2 + (j - kWPartW2) : kMlpW3 + (j - kWPartW3));
+    if (!kAdam) {
+        grad[p] = gr;
+        return;
     }
-    const int s0 = blockIdx.y * kWrGroup;
-    float v[kWrGroup];
-#pragma unroll
-    for (int u = 0; u < kWrGroup; ++u) v[u] = s0 + u < n_slices ? wpart[(size_t)(s0 + u) * kWPart + j] : 0.f;
-    float sum = 0.f;
-#pragma unroll
-    for (int u = 0; u < kWrGroup; ++u) sum += v[u];
-    atomicAdd(grad + dst, sum);
-}
-
-// One Adam step on the FP32 master parameters; re-packs the bf16 operand
-// fragments and clears the gradient for the next step.
-__global__ void k_mlp_adam(float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v,
-                           float* __restrict__ grad, uint16_t* __restrict__ blob, MlpAdam A) {
-    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < kMlpParams; p += gridDim.x * blockDim.x) {
-        float gr = grad[p];
-        grad[p] = 0.f;
-        float mm = A.beta1 * m[p] + (1.0f - A.beta1) * gr;
-        float vv = A.beta2 * v[p] + (1.0f - A.beta2) * gr * gr;
-        m[p] = mm;
-        v[p] = vv;
-        float mh = mm / A.bias1, vh = vv / A.bias2;
-        float w = theta[p] - A.lr * mh / (sqrtf(vh) + A.eps);
-        theta[p] = w;
-        pack_param(blob, p, w);
-    }
+    float mm = A.beta1 * m[p] + (1.0f - A.beta1) * gr;
+    float vv = A.beta2 * v[p] + (1.0f - A.beta2) * gr * gr;
+    m[p] = mm;
+    v[p] = vv;
+    float mh = mm / A.bias1, vh = vv / A.bias2;
+    float w = theta[p] - A.lr * mh / (sqrtf(vh) + A.eps);
+    theta[p] = w;
+    pack_param(blob, p, w);
 }
 
 __global__ void k_mlp_set_norm(MlpNorm* norm, float mu, float sigma) {
@@ -627,28 +645,29 @@ static int blocks_for(int64_t n, int per_block, int cap) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(b, cap));
 }
 
+// blocks of the training kernel: one per CU, at most
+static int train_blocks(int tiles) { return blocks_for(tiles, kTrainWaves, 256); }
+
 hipError_t mlp_alloc(Mlp& m, int32_t max_batch) {
     m.max_batch = max_batch;
-    m.npad = (max_batch + 15) & ~15;
     hipError_t e = hipMalloc(&m.theta, 4 * (size_t)kMlpParams);
     if (e == hipSuccess) e = hipMalloc(&m.m, 4 * (size_t)kMlpParams);
     if (e == hipSuccess) e = hipMalloc(&m.v, 4 * (size_t)kMlpParams);
-    if (e == hipSuccess) e = hipMalloc(&m.grad, 4 * (size_t)kMlpParams);
     if (e == hipSuccess) e = hipMalloc(&m.blob, 2 * (size_t)kFragAll);
     if (e == hipSuccess) e = hipMalloc(&m.norm, sizeof(MlpNorm));
     if (e == hipSuccess) e = hipMalloc(&m.loss, sizeof(float));
     if (e == hipSuccess) e = hipMalloc(&m.moments, 2 * sizeof(double));
-    if (e == hipSuccess) e = hipMalloc(&m.acts, 2 * (size_t)(kMlpIn + 5 * kMlpWidth) * m.npad);
+    const int tiles = (max_batch + 15) / 16;
+    if (e == hipSuccess) e = hipMalloc(&m.acts, 2 * (size_t)kRowsTile * 16 * tiles);
     // one partial row per wave of the training kernel at its largest grid
-    m.max_waves = 4 * std::max(1, std::min((m.npad / 16 + 15) / 16, 1 << 16));
-    if (e == hipSuccess) e = hipMalloc(&m.part, 4 * (size_t)kPartStride * m.max_waves);
-    m.max_slices = (m.npad + kWgSlice - 1) / kWgSlice;
+    if (e == hipSuccess) e = hipMalloc(&m.part, 4 * (size_t)kPartStride * kTrainWaves * train_blocks(tiles));
+    m.max_slices = (tiles * 16 + kWgSlice - 1) / kWgSlice;
     if (e == hipSuccess) e = hipMalloc(&m.wpart, 4 * (size_t)kWPart * m.max_slices);
     return e;
 }
 
 void mlp_free(Mlp& m) {
-    void* ps[] = {m.theta, m.m, m.v, m.grad, m.blob, m.norm, m.loss, m.moments, m.acts, m.part, m.wpart};
+    void* ps[] = {m.theta, m.m, m.v, m.blob, m.norm, m.loss, m.moments, m.acts, m.part, m.wpart};
     for (void* p : ps)
         if (p) (void)hipFree(p);
     m = Mlp();
@@ -659,7 +678,6 @@ hipError_t mlp_set_weights(Mlp& m, const float* host_theta, hipStream_t s) {
     if (e != hipSuccess) return e;
     e = hipMemsetAsync(m.m, 0, 4 * (size_t)kMlpParams, s);
     if (e == hipSuccess) e = hipMemsetAsync(m.v, 0, 4 * (size_t)kMlpParams, s);
-    if (e == hipSuccess) e = hipMemsetAsync(m.grad, 0, 4 * (size_t)kMlpParams, s);
     if (e == hipSuccess) e = hipMemsetAsync(m.blob, 0, 2 * (size_t)kFragAll, s);
     if (e == hipSuccess) e = hipMemsetAsync(m.loss, 0, sizeof(float), s);
     if (e != hipSuccess) return e;
@@ -710,8 +728,8 @@ hipError_t mlp_infer(const Mlp& m, const float* pos, int pos_stride, const float
     return hipGetLastError();
 }
 
-// gradient of the mean loss over one batch into m.grad (accumulated; the
-// Adam step clears it) and the loss sum into m.loss
+// gradient of the mean loss over one batch, left as parts for mlp_adam or
+// mlp_write_gradient, which also add its loss sum to m.loss
 hipError_t mlp_gradient(Mlp& m, const float* pos, int pos_stride, const float* nrm, int nrm_stride,
                         const float* target, const int32_t* pool_dev, int32_t pool_host, int32_t batch, int sample,
                         uint32_t k0, uint32_t k1, const OctParams* box, hipStream_t s) {
@@ -724,21 +742,17 @@ hipError_t mlp_gradient(Mlp& m, const float* pos, int pos_stride, const float* n
     B.k0 = k0;
     B.k1 = k1;
     B.step = (uint32_t)m.step;
-    const int npad = (batch + 15) & ~15;
-    const int tiles = npad / 16;
-    const int blocks = blocks_for(tiles, 16, 1 << 16);
-    const int n_waves = 4 * blocks;
-    if (n_waves > m.max_waves) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_mlp_train_fb, dim3(blocks), dim3(256), 0, s, (const uint16_t*)m.blob, (const float*)m.theta,
-                       (const MlpNorm*)m.norm, B, m.acts, npad, m.part);
-    const int slices = (npad + kWgSlice - 1) / kWgSlice;
-    if (slices > m.max_slices) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_mlp_wgrad, dim3(kWgLayers + kWgReduce, slices), dim3(64), 0, s, (const uint16_t*)m.acts,
-                       npad, m.grad, (const float*)m.part, n_waves, m.loss, m.wpart);
-    hipLaunchKernelGGL(k_mlp_wreduce, dim3((kWPart + 255) / 256, (slices + kWrGroup - 1) / kWrGroup), dim3(256), 0, s,
-                       (const float*)m.wpart, slices, m.grad);
+    const int tiles = (batch + 15) / 16, blocks = train_blocks(tiles);
+    hipLaunchKernelGGL(k_mlp_train_fb, dim3(blocks), dim3(64 * kTrainWaves), 0, s, (const uint16_t*)m.blob,
+                       (const float*)m.theta, (const MlpNorm*)m.norm, B, m.acts, tiles, m.part);
+    m.slices = (16 * tiles + kWgSlice - 1) / kWgSlice;
+    if (m.slices > m.max_slices) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_mlp_wgrad, dim3((m.slices + 7) / 8 * 8 * kWgJobs), dim3(64), 0, s, (const uint16_t*)m.acts,
+                       tiles, m.slices, (const float*)m.part, kTrainWaves * blocks, m.wpart);
     return hipGetLastError();
 }
+
+constexpr int kReduceGrid = kWPart / 32;
 
 hipError_t mlp_adam(Mlp& m, float lr, float beta1, float beta2, float eps, hipStream_t s) {
     m.step += 1;
@@ -749,8 +763,14 @@ hipError_t mlp_adam(Mlp& m, float lr, float beta1, float beta2, float eps, hipSt
     A.eps = eps;
     A.bias1 = (float)(1.0 - std::pow((double)beta1, (double)m.step));
     A.bias2 = (float)(1.0 - std::pow((double)beta2, (double)m.step));
-    hipLaunchKernelGGL(k_mlp_adam, dim3(blocks_for(kMlpParams, 256, 64)), dim3(256), 0, s, m.theta, m.m, m.v, m.grad,
-                       m.blob, A);
+    hipLaunchKernelGGL(k_mlp_reduce<true>, dim3(kReduceGrid), dim3(256), 0, s, (const float*)m.wpart, m.slices, m.loss,
+                       (float*)nullptr, m.theta, m.m, m.v, m.blob, A);
+    return hipGetLastError();
+}
+
+hipError_t mlp_write_gradient(Mlp& m, float* grad, hipStream_t s) {
+    hipLaunchKernelGGL(k_mlp_reduce<false>, dim3(kReduceGrid), dim3(256), 0, s, (const float*)m.wpart, m.slices, m.loss,
+                       grad, (float*)nullptr, (float*)nullptr, (float*)nullptr, (uint16_t*)nullptr, MlpAdam{});
     return hipGetLastError();
 }
 

@@ -4236,7 +4236,6 @@ static neb_status mlp_batch_grad(neb_mlp h, const float* q, const float* nrm, co
                                  hipStream_t s) {
     if (!h || !q || !nrm || !t) return fail(NEB_ERR_INVALID_ARG, "null pointer");
     if (n < 1 || n > h->m.max_batch) return fail(NEB_ERR_INVALID_ARG, "batch size out of range (1..max_batch)");
-    HIP_TRY(hipMemsetAsync(h->m.loss, 0, sizeof(float), s));
     HIP_TRY(mlp_gradient(h->m, q, 3, nrm, 3, t, nullptr, n, n, 0, 0u, 0u, nullptr, s));
     return NEB_OK;
 }
@@ -4247,8 +4246,8 @@ extern "C" neb_status neb_mlp_gradient(neb_mlp h, const float* q, const float* n
     hipStream_t s = (hipStream_t)stream;
     neb_status st = mlp_batch_grad(h, q, nrm, log_rho, n, s);
     if (st != NEB_OK) return st;
-    HIP_TRY(hipMemcpyAsync(grad, h->m.grad, 4 * (size_t)kMlpParams, hipMemcpyDeviceToDevice, s));
-    HIP_TRY(hipMemsetAsync(h->m.grad, 0, 4 * (size_t)kMlpParams, s));
+    HIP_TRY(hipMemsetAsync(h->m.loss, 0, sizeof(float), s));
+    HIP_TRY(mlp_write_gradient(h->m, grad, s));
     float sum = 0.f;
     HIP_TRY(hipStreamSynchronize(s));
     HIP_TRY(hipMemcpy(&sum, h->m.loss, sizeof(float), hipMemcpyDeviceToHost));
