@@ -145,6 +145,30 @@ struct Sample {
     int ev;      // 1 scatter, 2 reflect, 3 refract, 0 failed
 };
 
+// bsdf_f and the densities of both directions, of wo given wi and of wi given
+// wo, of a material that is not specular: one half vector and one normal
+// distribution for the three
+__device__ __forceinline__ f3 bsdf_both(const neb_material& m, f3 n, f3 wi, f3 wo, float& p_wo, float& p_wi) {
+    const float ci = dot3(n, wi), co = dot3(n, wo);
+    const f3 alb = load3(m.albedo);
+    p_wo = p_wi = 0.f;
+    if (ci * co <= 0.f) return mk3(0.f, 0.f, 0.f);
+    if (m.type == NEB_MAT_LAMBERT) {
+        p_wo = fabsf(co) * (1.0f / NEB_PI);
+        p_wi = fabsf(ci) * (1.0f / NEB_PI);
+        return alb * (1.0f / NEB_PI);
+    }
+    if (m.type == NEB_MAT_GGX) {
+        const f3 ns = ci > 0.f ? n : -n;
+        const f3 h = normalize3(wi + wo);
+        const float cm = dot3(h, ns), D = ggx_d(m.alpha, cm);
+        p_wo = D * cm / (4.0f * fabsf(dot3(wo, h)));
+        p_wi = D * cm / (4.0f * fabsf(dot3(wi, h)));
+        const float G = ggx_g1(m.alpha, fabsf(ci)) * ggx_g1(m.alpha, fabsf(co));
+        return alb * (D * G / (4.0f * fabsf(ci) * fabsf(co)));
+    }
+    return mk3(0.f, 0.f, 0.f);
+}
 __device__ __forceinline__ Sample bsdf_sample(const neb_material& m, f3 n, f3 wi, const U4& u) {
     Sample s;
     s.ev = 0;

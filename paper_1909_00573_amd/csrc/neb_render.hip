@@ -111,11 +111,10 @@ struct SceneInfo {
 };
 
 // Merge grid keyed by (hash of scene and cell, depth class): the records of
-// one cell are ordered by view-vertex depth class (depth - 1, the last of
-// the D classes also holding every deeper vertex), so the vertices a photon
+// one cell are ordered by view-vertex depth class, so the vertices a photon
 // after j bounces may merge with (depth <= maxlen - 1 - j) lie in one
-// contiguous prefix; only the last class's deeper vertices are filtered by
-// the depth each entry carries.
+// contiguous prefix; the last class's deeper vertices are filtered by the
+// depth each entry carries.
 struct Grid {
     int32_t* count;   // T * D + 1 entries (the last stays 0); zeroed by the scan that reads them
     int32_t* start;   // T * D + 1 entries
@@ -125,7 +124,7 @@ struct Grid {
                       // (n, tag), (wo, B), (tau, g), (pixel, -, -, -)
     int32_t* sums;    // scan block sums, all levels
     int32_t T;        // hash buckets (power of two)
-    int32_t D;        // depth classes: 8 (a cell's row is one aligned 32-byte sector)
+    int32_t D;        // depth classes: 2
 };
 
 // prefix sums are scanned in tiles of kScanTile elements (a tile per block
@@ -1320,8 +1319,11 @@ __global__ void __launch_bounds__(256) k_nee_recycle(RenderArgs A, VertexStore V
 // scan, which zeroes the counts for the next iteration -> scatter to
 // start[key] + rank)
 // ---------------------------------------------------------------------------
+// Depths 1 to 4 are one class, the deeper ones the other: a photon of the
+// later bounces, which may only merge with shallow vertices, skips the second.
+__device__ __forceinline__ int grid_class(const Grid& G, int depth) { return min((depth - 1) >> 2, G.D - 1); }
 __device__ __forceinline__ int64_t grid_key(const Grid& G, uint32_t h, int depth) {
-    return (int64_t)h * G.D + (min(depth, G.D) - 1);
+    return (int64_t)h * G.D + grid_class(G, depth);
 }
 
 __global__ void __launch_bounds__(256) k_grid_count(const neb_material* mats, const SceneInfo* sc, VertexStore V,
@@ -1500,25 +1502,41 @@ __global__ void __launch_bounds__(256) k_bin_scatter(const int32_t* __restrict__
     }
 }
 
+// a value that every lane holds, in scalar registers
+__device__ __forceinline__ unsigned long long uniform64(unsigned long long v) {
+    return (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v) |
+           ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32);
+}
+// bits of m below the lane's own
+__device__ __forceinline__ int lanes_below(unsigned long long m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+}
+
 // ---------------------------------------------------------------------------
 // photon bounce: merge with view vertices around the hit, then scatter.
 // A wave takes 64 photons, one per lane; each lane finds the candidate
 // ranges of its photon's cells.  The wave then walks the concatenation of
 // all 64 photons' candidate lists together: consecutive lanes take
-// consecutive candidates (a wave-wide scan of the lanes' counts maps a
-// position back to its photon and cell), so the candidate loads of a step
-// are contiguous runs of a cell's records and the number of steps follows
-// the wave's total, not its longest list.  Accepted (photon, vertex) pairs
+// consecutive candidates, so the candidate loads of a step are contiguous
+// runs of a cell's records and the number of steps follows the wave's
+// total, not its longest list.  A position's range is the number of ranges
+// that begin up to it: one bit per position marks the beginnings, and a
+// lane counts the bits below its own (a binary search over the lanes' sums
+// and then over the photon's cells, which this replaced, took fourteen
+// dependent LDS reads: batch 815 -> 727 us per iteration alone; the room,
+// bound by the lines it reads, 1645 -> 1630).  Accepted (photon, vertex) pairs
 // are compacted into an LDS queue and evaluated 64 at a time by the whole
 // wave, so the BSDF, the MIS weight and the image atomics run with every
-// lane busy instead of with the ~15 % of candidates that are accepted.
+// lane busy instead of with the ~15 % of candidates that are accepted; the
+// BSDF and its two densities share their parts (batch 727 -> 700 us, room
+// 1630 -> 1615).
 // One wave per block.
 // ---------------------------------------------------------------------------
 // Photons are taken in the spatial order `order` (null: queue order).  Blocks
 // b, b + 8, b + 16, ... run on one XCD (round-robin dispatch), so each XCD
 // takes one contiguous eighth of the ordered photons: neighbouring photons
 // then share that XCD's L2 for their cells and candidates.
-// Four waves per SIMD (at most 128 VGPRs): with 10 000 bytes of LDS per
+// Four waves per SIMD (at most 128 VGPRs): with 10 240 bytes of LDS per
 // block that is also the LDS limit, 16 resident blocks per CU.  Alone the
 // kernel runs as fast with three; beside the closest hits and the camera
 // pass the fourth keeps more of its loads in flight.
@@ -1529,9 +1547,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) k_
     __shared__ float te[64];      // per lane's photon: weight of its own technique in the MIS denominator
     __shared__ float sval[64][3]; // contributions of a flushed batch
     __shared__ int sdst[64];      // their pixels (bit 30: light-photon image), -1 for none
-    __shared__ int wbase[65];     // exclusive scan of the lanes' candidate counts
-    __shared__ int coff[64][8];   // per lane's cell c: first record minus its offset in the lane's list
-    __shared__ int cend[64][8];   // per lane's cell c: end of its range in the lane's list
+    __shared__ int2 range[512];   // the wave's candidate ranges: first record minus its position in the list, photon
+    __shared__ unsigned long long mark[64];  // bit per position of a window of 4096: a range begins there
     __shared__ float4 ty[64];     // per lane's photon: hit point, r^2
     __shared__ int tsid[64];      // per lane's photon: scene | deepest mergeable depth << 24
     const int lane = threadIdx.x;
@@ -1563,10 +1580,11 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) k_
             if (k <= (km & 255)) {
                 const neb_material& mv = S.mats[tag_mat(tg)];
                 const f3 nv = xyz(v1), wv = xyz(v2), wd = xyz(t0);
-                const f3 f = bsdf_f(mv, nv, wv, wd);
+                float p_to, p_from;
+                const f3 f = bsdf_both(mv, nv, wv, wd, p_to, p_from);
                 if (!is_zero3(f)) {
-                    const float T = bsdf_pdf(mv, nv, wv, wd) * t0.w;
-                    const float C = te[pr.x] + ((k >= 2) ? bsdf_pdf(mv, nv, wd, wv) * v3.w * v2.w : 0.f);
+                    const float T = p_to * t0.w;
+                    const float C = te[pr.x] + ((k >= 2) ? p_from * v3.w * v2.w : 0.f);
                     dst = pix | ((km & 256) ? (1 << 30) : 0);
                     val = xyz(v3) * f * xyz(t1) * (1.0f / (C + T));
                     ++merges;
@@ -1672,7 +1690,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) k_
                 if (use) {
                     int64_t key = grid_key(G, hc, 1);
                     e0 = G.start[key];
-                    e1 = G.start[key + min(kmax, G.D)];
+                    e1 = G.start[key + grid_class(G, kmax) + 1];
                     ++looked;
                 }
                 lo[c] = e0;
@@ -1687,9 +1705,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) k_
         cells += looked;
         int total = pre[8];
         cands += (unsigned)total;
-        // the wave's candidate list: photon p's entries start at wbase[p];
-        // its cell c covers [cend[p][c-1], cend[p][c]) of them, record
-        // coff[p][c] + position
+        // the wave's candidate list is the concatenation of its lanes'
+        // ranges that hold records, each with the position it begins at
         int incl = total;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
@@ -1697,38 +1714,51 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) k_
             if (lane >= off) incl += v;
         }
         const int wsum = __shfl(incl, 63, 64);
-        wbase[lane + 1] = incl;
-        if (lane == 0) wbase[0] = 0;
+        const int first = incl - total;
+        {
+            int held = 0;
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            coff[lane][c] = lo[c] - pre[c];
-            cend[lane][c] = pre[c + 1];
+            for (int c = 0; c < 8; ++c) held += pre[c + 1] > pre[c];
+            int r = 0;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) r += __popcll(__ballot((held >> b) & 1) & below) << b;
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+                if (pre[c + 1] > pre[c]) range[r++] = make_int2(lo[c] - pre[c] - first, lane);
         }
         ty[lane] = f4(y, r2);
         tsid[lane] = sid | (max(kmax, 0) << 24);
-        __syncthreads();
         // four positions per lane per step, their loads independent (measured
         // on the room alone: 4 and 8 equal, both 22 % faster than one photon's
         // list per lane with eight loads in flight; beside the other streams
         // four is 1 % faster, sixteen 25 % slower)
         constexpr int kU = 4;
+        int begun = -1;  // ranges that begin before the step, less one
         for (int t = 0; t < wsum; t += 64 * kU) {
+            if ((t & 4095) == 0) {
+                __syncthreads();
+                mark[lane] = 0ull;
+                __syncthreads();
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const int s = first + pre[c] - t;
+                    if (pre[c + 1] > pre[c] && (unsigned)s < 4096u) atomicOr(&mark[s >> 6], 1ull << (s & 63));
+                }
+                __syncthreads();
+            }
             int ev[kU], pv[kU];
             float4 cd[kU];
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
                 const int kk = t + u * 64 + lane;
+                const unsigned long long m = uniform64(mark[((t >> 6) + u) & 63]);
+                const int r = begun + (int)(m & 1) + lanes_below(m >> 1);
+                begun += __popcll(m);
                 int e = -1, p = 0;
                 if (kk < wsum) {
-                    // p: the last photon whose list starts at or before kk
-#pragma unroll
-                    for (int st = 32; st; st >>= 1)
-                        if (wbase[p + st] <= kk) p += st;
-                    const int rk = kk - wbase[p];
-                    int c = 0;
-#pragma unroll
-                    for (int q = 0; q < 7; ++q) c += cend[p][q] <= rk;
-                    e = coff[p][c] + rk;
+                    const int2 g = range[r];
+                    e = g.x + kk;
+                    p = g.y;
                 }
                 ev[u] = e;
                 pv[u] = p;
@@ -1741,8 +1771,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) k_
                 if (ev[u] >= 0) {
                     const float4 yp = ty[pv[u]];
                     f3 dv = xyz(cd[u]) - xyz(yp);
-                    // a bucket may also hold another scene's cell, and the
-                    // last depth class deeper vertices than the photon may reach
+                    // a bucket may also hold another scene's cell, and a
+                    // depth class deeper vertices than the photon may reach
                     const int w = fbits(cd[u].w), ts = tsid[pv[u]];
                     acc = dot3(dv, dv) < yp.w && (w & 0xFFFFFF) == (ts & 0xFFFFFF) && (w >> 24) <= (ts >> 24);
                 }
@@ -2498,11 +2528,19 @@ extern "C" neb_status neb_create_batch(const neb_params* params, int32_t n_scene
     }
     if (c->flags & NEB_FLAG_SINGLE_THREAD_OCTREE) ALLOC(c->slots, slot_cap);
     if (c->flags & NEB_FLAG_RECORD_PATHS) ALLOC(c->recs, npix * L);
-    // eight depth classes whatever the path length: a cell's row is one
-    // aligned 32-byte sector, and the table's size does not grow with the
-    // path length (longer paths share the last class)
-    c->G.D = 8;
-    c->G.T = (int32_t)std::max<uint64_t>(1024, std::min<uint64_t>(next_pow2((uint64_t)vcap) / 2, 1u << 23));
+    // Two depth classes and about as many buckets as vertices: a cell's row
+    // is 8 bytes, so that the 2 x 2 x 2 cells of a Morton octet lie in one
+    // 64-byte sector.  With eight classes of half as many buckets the table
+    // was twice as large (four classes: as large) and a hit's lookups spread
+    // over more lines; fewer candidates did not make up for it.  Merges per
+    // iteration, room / 12 x 12-lot city / batch, us: eight 1615 / 520 / 695,
+    // four 1567 / 483 / 700, two 1549 / 454 / 664, one 1595 / 441 / 670; grid
+    // build 293 / 830 / 430, 277 / 623 / 398, 281 / 542 / 401, 272 / 493 / 401.
+    // Half the buckets: room 1581, batch 689 (blocks share buckets).
+    const uint64_t around = next_pow2((uint64_t)vcap);
+    c->G.D = 2;
+    c->G.T = (int32_t)std::max<uint64_t>(1024, std::min<uint64_t>(around, 1u << 23));
+    const int32_t half = (int32_t)std::max<uint64_t>(1024, std::min<uint64_t>(around / 2, 1u << 23));
     int64_t gkeys = (int64_t)c->G.T * c->G.D + 1;
     ALLOC(c->G.count, gkeys);
     ALLOC(c->G.start, gkeys);
@@ -2511,7 +2549,7 @@ extern "C" neb_status neb_create_batch(const neb_params* params, int32_t n_scene
     ALLOC(c->G.mrec, 4 * vcap);
     ALLOC(c->G.sums, scan_scratch(gkeys));
     if (c->recycle) {
-        c->ng.T = c->G.T;
+        c->ng.T = half;
         ALLOC(c->ng.count, (int64_t)c->ng.T + 1);
         ALLOC(c->ng.start, (int64_t)c->ng.T + 1);
         ALLOC(c->ng.pts, vcap);
@@ -2523,7 +2561,7 @@ extern "C" neb_status neb_create_batch(const neb_params* params, int32_t n_scene
         }
     }
     if (c->density_mode == NEB_DENSITY_RADIUS || c->density_mode == NEB_DENSITY_KNN) {
-        c->dg.T = c->G.T;
+        c->dg.T = half;
         ALLOC(c->dg.count, (int64_t)c->dg.T + 1);
         ALLOC(c->dg.start, (int64_t)c->dg.T + 1);
         ALLOC(c->dg.pts, vcap);
