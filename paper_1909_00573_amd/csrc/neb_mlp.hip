@@ -546,7 +546,9 @@ __global__ void __launch_bounds__(64) k_mlp_wgrad(const uint16_t* __restrict__ a
 
 // Sums the slices' parts, 32 parameters per block of 256 threads (eight
 // threads per parameter; whole 128-byte lines), eight slices at a time in order
-// and then the groups in order, and either takes one Adam step on the FP32
+// and then the groups in order (in FP64: the groups used to be added in any
+// order, by atomics, and this stays in the middle of what that could give),
+// and either takes one Adam step on the FP32
 // master parameters and re-packs the bf16 operand fragments (kAdam), or writes
 // the gradient.  The loss sum is added to *loss.  One launch for the sums
 // (4.6 us, with atomics), Adam (4.7) and the fills (3.6): 6 us.
@@ -559,7 +561,7 @@ __global__ void __launch_bounds__(256) k_mlp_reduce(const float* __restrict__ wp
     __shared__ float sh[256 / 32][32];
     const int c = threadIdx.x & 31, q = threadIdx.x >> 5;
     const int p = blockIdx.x * 32 + c;
-    float gr = 0.f;
+    double total = 0.0;
     for (int s0 = 0; s0 < n_slices; s0 += kWrGroup * (256 / 32)) {
         // this thread's group of the next eight
         const int s = s0 + kWrGroup * q;
@@ -574,10 +576,11 @@ __global__ void __launch_bounds__(256) k_mlp_reduce(const float* __restrict__ wp
         if (q == 0)
 #pragma unroll
             for (int u = 0; u < 256 / 32; ++u)
-                if (s0 + kWrGroup * u < n_slices) gr += sh[u][c];
+                if (s0 + kWrGroup * u < n_slices) total += (double)sh[u][c];
         __syncthreads();
     }
     if (q != 0 || p > kWPartLoss) return;
+    const float gr = (float)total;
     if (p == kWPartLoss) {
         *loss += gr;
         return;

@@ -1,40 +1,49 @@
 // Lock-free sparse density octree (Sec. 5 of the paper, class of Appendix B)
-// on gfx950: device-scope atomics on an int32 node pool, compare-and-swap
-// counting and splits allocated with one fetch-add.  No lane ever waits for
-// another lane.  Several octrees (one per scene of a batch) can share one
-// pool; each owns the words [root, end) and has its own OctState.
+// on gfx950: device-scope atomics on an int32 node pool and splits allocated
+// with one fetch-add.  No lane ever waits for another lane.  Several octrees
+// (one per scene of a batch) can share one pool; each owns the words
+// [root, end) and has its own OctState.
 //
 // Node word: >= 0 is a count (bit 30 marks a leaf whose split could not be
 // allocated; it keeps counting), < 0 is minus the index of the first of 8
 // consecutive children.
 //
 // Differences from the listing, and why:
+//  - the listing counts in the node word with compare-and-swap.  Lanes at
+//    one leaf then succeed one per round trip to memory: a leaf that takes
+//    a thousand deposits holds the launch up for milliseconds.  Here the
+//    deposits of a call are added to a second word per node (`fresh`, zero
+//    between calls) with fetch-add, which needs no earlier value, and join
+//    the node words when the call ends (k_oct_fold).  While a call runs, a
+//    node word only ever changes from the count it began with to a pointer
+//    or to a failed leaf, so any cached copy of a count is the right one.
+//    The deposits whose fetch-add returned less than the leaf's free room
+//    are counted, the group that fills the room splits the leaf, and what
+//    was added beyond is taken off again;
 //  - the listing lets a thread that finds a full leaf without a published
 //    child pointer spin until the pointer appears.  On a 64-wide wavefront
 //    the splitter may sit in the same wave as the spinner, and the
 //    compiler places the split (which follows the loop-exiting CAS) after
 //    the loop's reconvergence point: the wave deadlocks.  Here the lanes of
-//    a wave that reach the same node word add their count with one CAS
-//    (capped at the split threshold), the lane whose addition fills the
-//    leaf splits it on the spot, and the lanes beyond the cap follow the
-//    pointer their own wave has just published; so a full leaf without a
-//    pointer was always filled by another wave.  Such a deposit is deferred
-//    to a queue retried by the next round, once that wave's split is
-//    certainly published: rounds 1 .. kOctLaunchRounds - 1 are launches of
-//    their own (the kernel boundary), later rounds run in one block,
-//    separated by the block's barrier and an agent-scope acquire.  A deposit is deferred at
-//    most once per level, so kOctMaxDepth + 1 retry rounds bound the work.
-//    (Re-reading the word a bounded number of times instead was measured
-//    slower: a wave keeps looping while any lane waits);
-//  - no increment is overwritten by the pointer store (deposits never
-//    count past the threshold), so the ledger
+//    a wave that reach the same leaf add their number with one atomic, the
+//    group whose addition fills the leaf splits it on the spot and goes on
+//    from the pointer it has just published; anyone else at a full leaf
+//    reads the word once more, and if the pointer is not there yet the
+//    deposit is deferred to a queue retried by the next round, once that
+//    split is certainly published: rounds 1 .. kOctLaunchRounds - 1 are
+//    launches of their own (the kernel boundary), later rounds run in one
+//    block, separated by the block's barrier and an agent-scope acquire.  A
+//    deposit is deferred at most once per level, so kOctMaxDepth + 1 retry
+//    rounds bound the work;
+//  - no count is lost to the pointer store (a leaf takes exactly its room,
+//    and what it took is accounted for by its split), so the ledger
 //        S = sum(leaf counts) - 4 * sum(iteration of each allocated block)
 //    equals the number of deposits exactly;
 //  - the splitter writes the eight children's start count (the current
-//    iteration, i.e. parent/4) before it publishes the pointer, instead of
-//    prefilling every unused node per iteration;
+//    iteration, i.e. parent/4) into their `fresh` words before it publishes
+//    the pointer, instead of prefilling every unused node per iteration;
 //  - node words are read with cacheable loads; a negative word never
-//    changes again and every other decision is validated by the CAS;
+//    changes again;
 //  - nodes at depth 20 never split (FP32 positions cannot resolve finer
 //    cells).
 #include <algorithm>
@@ -70,9 +79,9 @@ struct SplitTally {
 // the eight children at the current iteration (parent / 4), then publish
 // the pointer.  Returns the node word afterwards: the child pointer, or
 // `full` marked as a failed split.
-__device__ __forceinline__ int32_t oct_make_children(int32_t* nodes, const OctParams& P, const OctDyn& D,
-                                                     int32_t idx, int level, int32_t full, int32_t child,
-                                                     SplitTally& T) {
+__device__ __forceinline__ int32_t oct_make_children(int32_t* nodes, int32_t* counts, const OctParams& P,
+                                                     const OctDyn& D, int32_t idx, int level, int32_t full,
+                                                     int32_t child, SplitTally& T) {
     if (child >= P.end) {
         __hip_atomic_fetch_or(nodes + idx, kOctFailed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         T.failed += 1;
@@ -80,10 +89,10 @@ __device__ __forceinline__ int32_t oct_make_children(int32_t* nodes, const OctPa
     }
     // the wait retires the eight atomic writes (CDNA tracks them in vmcnt)
     // before the pointer is published, so a lane that follows the pointer
-    // and CASes a child compares against the started count
+    // and adds to a child adds to the started count
 #pragma unroll
     for (int c = 0; c < 8; ++c)
-        __hip_atomic_exchange(nodes + child + c, D.iter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_exchange(counts + child + c, D.iter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __hip_atomic_exchange(nodes + idx, -child, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     T.iter_sum += (unsigned long long)D.iter;
@@ -92,7 +101,9 @@ __device__ __forceinline__ int32_t oct_make_children(int32_t* nodes, const OctPa
 }
 
 // next free block of n blocks of 8 in an octree, or P.end if the pool is
-// full (a full pool is seen with a plain read, without an atomic)
+// full (a full pool is seen with a plain read, without an atomic).  Every
+// split of the tree passes here, and atomics on one word run one after
+// another: this bounds a reset tree's first call.
 __device__ __forceinline__ int32_t oct_alloc(OctState* st, const OctParams& P, int n) {
     if (__hip_atomic_load(&st->alloc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= P.end) return P.end;
     return atomicAdd(&st->alloc, 8 * n);
@@ -129,7 +140,7 @@ __device__ __forceinline__ int oct_insert(int32_t* nodes, OctState* st, const Oc
         }
         if (can_split && cnt + 1 == D.split_count) {
             SplitTally T;
-            oct_make_children(nodes, P, D, idx, level, v + 1, oct_alloc(st, P, 1), T);
+            oct_make_children(nodes, nodes, P, D, idx, level, v + 1, oct_alloc(st, P, 1), T);
             flush_tally(st, T);
         }
         return kInsCounted;
@@ -137,18 +148,34 @@ __device__ __forceinline__ int oct_insert(int32_t* nodes, OctState* st, const Oc
     return kInsDeferred;
 }
 
+struct WaveGroups {
+    int slot[128];  // a lane at the leaves that share the slot
+    int size[64];   // per leading lane: lanes of its group
+};
+
+// LDS written by some lanes of the wave, to be read by others
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Wave-cooperative deposit of one point per lane (lanes may belong to
-// different octrees of the pool).  Each pass: lanes that reach the same
-// node word with the same observed value form a group, and the group's
-// first lane adds the group's size (capped at the split threshold) with one
-// CAS; then every group whose addition filled its leaf splits, with one
-// block allocation per octree for all of the wave's splits of the pass.
-// The lanes beyond a cap follow the pointer their own wave has just
-// published (nobody waits for anybody).  Lanes that find a leaf filled by
-// another wave, whose split may still be in flight, defer to the next
-// launch.  Must be called by all lanes of the wave.
-__device__ __forceinline__ int oct_insert_wave(int32_t* nodes, OctState* st, const OctParams& P, const OctDyn& D,
-                                               bool has, f3 p, SplitTally& tally) {
+// different octrees of the pool).  Each pass: every lane descends to a leaf;
+// lanes at the same leaf form a group, whose leader adds the group's size to
+// the leaf's fresh count with one fetch-add; then every group whose addition
+// filled its leaf splits it, with one block allocation per octree for all of
+// the wave's splits of the pass.  Lanes that find a leaf filled by another
+// wave, whose split may still be in flight, defer to the next launch.  Must
+// be called by all lanes of the wave.
+//
+// Bound by the latency of the descent and of one atomic per group.  A
+// million deposits into a tree grown from 60 000 points, us: 450 with groups
+// formed one leader at a time (64 dependent shuffles in a wave of scattered
+// points) and compare-and-swap, 370 with the slots below, 82 with fetch-add;
+// into a tree grown from 3 000 points (hundreds of deposits per leaf) 3 150,
+// 2 570 and 85; the first call of a reset tree 2 450, 2 100 and 1 500.
+__device__ __forceinline__ int oct_insert_wave(int32_t* nodes, int32_t* fresh, OctState* st, const OctParams& P,
+                                               const OctDyn& D, bool has, f3 p, SplitTally& tally, WaveGroups& G) {
     const int lane = threadIdx.x & 63;
     const unsigned long long below = (1ull << lane) - 1ull;
     const unsigned long long stkey = (unsigned long long)(uintptr_t)st;
@@ -160,56 +187,51 @@ __device__ __forceinline__ int oct_insert_wave(int32_t* nodes, OctState* st, con
     int32_t v = active ? ld_node(nodes + idx) : 0;
     for (int step = 0; step < 4096; ++step) {
         if (!__any(active)) break;
-        if (active && v < 0) {
+        while (active && v < 0) {
             ++level;
             idx = child_index(q, level) - v;
             v = ld_node(nodes + idx);
         }
-        const bool grouped = active && v >= 0;
-        bool want = grouped;
-        unsigned long long pend = __ballot(want);
-        // phase 1: the lanes at the same word form a group (its first lane
-        // leads) and take m of its free counts; then every leader issues its
-        // group's CAS at once, so the wave waits for one atomic round trip,
-        // not one per group
-        int my_leader = lane, my_rank = 0, my_m = 0;
-        int lead_m = 0;  // this lane leads a group taking lead_m counts
-        bool lead_split = false;
-        while (pend) {
-            int leader = __ffsll((long long)pend) - 1;
-            int32_t lidx = __shfl(idx, leader, 64);
-            int32_t lv = __shfl(v, leader, 64);
-            int llevel = __shfl(level, leader, 64);
-            bool in = want && idx == lidx && v == lv;
-            unsigned long long gm = __ballot(in);
-            int k = __popcll(gm);
-            int32_t cnt = lv & kOctCountMask;
-            bool can_split = !(lv & kOctFailed) && llevel < kOctMaxDepth;
-            int m = can_split ? min(k, max(0, D.split_count - cnt)) : k;
-            if (in) {
-                my_leader = leader;
-                my_rank = __popcll(gm & below);
-                my_m = m;
+        const bool grouped = active;
+        // phase 1: lanes at the same leaf form a group.  Each writes its lane
+        // number into a slot chosen by the leaf's index; whoever is read back
+        // from it leads the lanes at its own leaf.  A group whose slot another
+        // leaf took tries a second slot, and if that is taken too its lanes
+        // lead themselves (two groups at one leaf are two waves to it).
+        int my_leader = lane;
+        bool lone = grouped;
+        for (int r = 0; r < 2; ++r) {
+            const uint32_t h = (uint32_t)idx * (r ? 0x9E3779B1u : 0x85EBCA77u) >> 25;
+            if (lone) G.slot[h] = lane;
+            wave_sync();
+            const int cand = lone ? G.slot[h] : lane;
+            const int32_t ci = __shfl(idx, cand, 64), cv = __shfl(v, cand, 64);
+            if (lone && ci == idx && cv == v) {
+                my_leader = cand;
+                lone = false;
             }
-            if (lane == leader) {
-                lead_m = m;
-                lead_split = can_split && cnt + m == D.split_count;
-            }
-            want = want && !in;
-            pend &= ~gm;
+            wave_sync();
         }
-        int l_ok = 0, l_split = 0;
-        int32_t l_cur = v, l_full = v;
-        if (lead_m > 0) {  // a leader's own idx and v are its group's
-            int32_t e = v;
-            l_ok = __hip_atomic_compare_exchange_strong(nodes + idx, &e, v + lead_m, __ATOMIC_RELAXED,
-                                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            l_cur = e;
-            l_full = v + lead_m;
-            l_split = l_ok && lead_split;
+        G.size[lane] = 0;
+        wave_sync();
+        int my_rank = 0;
+        if (grouped) my_rank = atomicAdd(&G.size[my_leader], 1);
+        wave_sync();
+        const int k = grouped ? G.size[my_leader] : 0;
+        const int32_t count = v & kOctCountMask;
+        const bool bounded = !(v & kOctFailed) && level < kOctMaxDepth;
+        const int limit = bounded ? D.split_count - count : INT32_MAX;  // deposits the leaf takes in this call
+        int l_room = 0;  // of the group's deposits, those the leaf took
+        bool l_split = false;
+        if (grouped && my_leader == lane && limit > 0) {
+            const int before = __hip_atomic_fetch_add(fresh + idx, k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            l_room = min(k, max(0, limit - before));
+            l_split = bounded && before < limit && before + k >= limit;
+            if (l_room < k)
+                __hip_atomic_fetch_add(fresh + idx, l_room - k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         // phase 2: the pass's splits, one allocation per octree
-        int32_t l_after = l_full;
+        int32_t l_after = v;
         unsigned long long spl = __ballot(l_split);
         while (spl) {
             int first = __ffsll((long long)spl) - 1;
@@ -219,26 +241,27 @@ __device__ __forceinline__ int oct_insert_wave(int32_t* nodes, OctState* st, con
             int32_t base = 0;
             if (lane == first) base = oct_alloc(st, P, __popcll(sm));
             base = __shfl(base, first, 64);
-            if (mine) l_after = oct_make_children(nodes, P, D, idx, level, l_full, base + 8 * __popcll(sm & below), tally);
+            if (mine) l_after = oct_make_children(nodes, fresh, P, D, idx, level, v, base + 8 * __popcll(sm & below), tally);
             spl &= ~sm;
         }
-        // phase 3: every grouped lane learns its group's outcome
-        int ok = __shfl(l_ok, my_leader, 64);
-        int32_t cur = __shfl(l_cur, my_leader, 64);
-        int32_t after = __shfl(l_after, my_leader, 64);
+        // phase 3: every lane learns its group's outcome
+        const int room = __shfl(l_room, my_leader, 64);
+        const int32_t after = __shfl(l_after, my_leader, 64);
         if (grouped) {
-            if (my_m == 0) {  // full leaf, split in flight: retry after the launch
-                result = kInsDeferred;
+            if (my_rank < room) {
+                result = kInsCounted;
                 active = false;
-            } else if (ok) {
-                if (my_rank < my_m) {
-                    result = kInsCounted;
-                    active = false;
-                } else {
-                    v = after;  // this wave split the leaf: go on from its new word
-                }
             } else {
-                v = cur;  // the word changed: retry with its current value
+                // a full leaf: this group split it, or someone else has or will
+                const int32_t now = after != v ? after
+                                               : __hip_atomic_load(nodes + idx, __ATOMIC_RELAXED,
+                                                                   __HIP_MEMORY_SCOPE_AGENT);
+                if (now != v) {
+                    v = now;
+                } else {  // its split is in flight: retry after the launch
+                    result = kInsDeferred;
+                    active = false;
+                }
             }
         }
     }
@@ -284,12 +307,14 @@ __device__ __forceinline__ int item_scene(const int32_t* scene_word, int stride,
 // [0, n) (items == nullptr) or the listed ones.  Positions are float3
 // (stride 3) or the xyz of float4 records (stride 4); the octree of an item
 // is read from scene_word.  Deferred items go to defer_out.
-__device__ __forceinline__ void oct_insert_pass(int32_t* nodes, OctState* states, const OctParams* prm,
+__device__ __forceinline__ void oct_insert_pass(int32_t* nodes, int32_t* fresh, OctState* states, const OctParams* prm,
                                                 const OctDyn& D, const float* __restrict__ pos, int stride,
                                                 const int32_t* __restrict__ scene_word, int shift,
                                                 const int32_t* __restrict__ items, int32_t n, int64_t t0,
                                                 int64_t step, int32_t* __restrict__ defer_out,
                                                 int32_t* defer_count) {
+    __shared__ WaveGroups groups[4];
+    WaveGroups& G = groups[threadIdx.x >> 6];
     int64_t nn = (n + step - 1) / step * step;  // uniform trip count per wave
     for (int64_t i = t0; i < nn; i += step) {
         bool has = i < n;
@@ -304,7 +329,7 @@ __device__ __forceinline__ void oct_insert_pass(int32_t* nodes, OctState* states
         }
         const OctParams P = prm[s];
         SplitTally tally;
-        int r = oct_insert_wave(nodes, states + s, P, D, has, pt, tally);
+        int r = oct_insert_wave(nodes, fresh, states + s, P, D, has, pt, tally, G);
         bool defer = has && r == kInsDeferred;
         oct_account(states, s, has && r == kInsCounted, has && r == kInsRejected, tally);
         int slot = wave_reserve(defer_count, defer);
@@ -316,7 +341,7 @@ __device__ __forceinline__ void oct_insert_pass(int32_t* nodes, OctState* states
 // kOctLaunchRounds - 1 (the items deferred in the round before) of a
 // deposit; the counter of the round after next is cleared here (three
 // counters rotate).
-__global__ void __launch_bounds__(256) k_oct_insert(int32_t* nodes, OctState* states, const OctParams* prm,
+__global__ void __launch_bounds__(256) k_oct_insert(int32_t* nodes, int32_t* fresh, OctState* states, const OctParams* prm,
                                                     const OctDyn* dyn, const float* __restrict__ pos, int stride,
                                                     const int32_t* __restrict__ scene_word, int shift,
                                                     const int32_t* __restrict__ items, const int32_t* n_dev,
@@ -326,7 +351,7 @@ __global__ void __launch_bounds__(256) k_oct_insert(int32_t* nodes, OctState* st
     const OctDyn D = *dyn;
     int32_t n = n_dev ? min(*n_dev, n_host) : n_host;
     if (D.stop_filling) return;
-    oct_insert_pass(nodes, states, prm, D, pos, stride, scene_word, shift, items, n,
+    oct_insert_pass(nodes, fresh, states, prm, D, pos, stride, scene_word, shift, items, n,
                     blockIdx.x * (int64_t)blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x, defer_out,
                     defer_count);
 }
@@ -339,7 +364,7 @@ __global__ void __launch_bounds__(256) k_oct_insert(int32_t* nodes, OctState* st
 // cnt[r % 3] and appends to list r & 1 counted by cnt[(r + 1) % 3].  Items
 // still deferred after the last round cannot occur (each round resolves at
 // least one level) and would be reported as lost.
-__global__ void __launch_bounds__(256) k_oct_insert_tail(int32_t* nodes, OctState* states, const OctParams* prm,
+__global__ void __launch_bounds__(256) k_oct_insert_tail(int32_t* nodes, int32_t* fresh, OctState* states, const OctParams* prm,
                                                          const OctDyn* dyn, const float* __restrict__ pos, int stride,
                                                          const int32_t* __restrict__ scene_word, int shift,
                                                          int32_t* defer0, int32_t* defer1, int32_t* cnt,
@@ -358,7 +383,7 @@ __global__ void __launch_bounds__(256) k_oct_insert_tail(int32_t* nodes, OctStat
         __syncthreads();
         const int32_t n = sn;
         if (n == 0) break;
-        oct_insert_pass(nodes, states, prm, D, pos, stride, scene_word, shift, (r & 1) ? defer0 : defer1, n,
+        oct_insert_pass(nodes, fresh, states, prm, D, pos, stride, scene_word, shift, (r & 1) ? defer0 : defer1, n,
                         threadIdx.x, blockDim.x, (r & 1) ? defer1 : defer0, out_cnt);
         __syncthreads();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
@@ -424,16 +449,32 @@ __global__ void k_oct_clear(int32_t* nodes, OctState* st, int32_t root, int32_t 
         int32_t v = nodes[i];
         if (v > 0) nodes[i] = 0;
     }
+    // the ledger restarts
+    if (blockIdx.x == 0 && threadIdx.x < kDepositStripes) st->deposits[threadIdx.x].v = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) st->block_iter_sum = 0;
 }
 
-// after clear: the ledger restarts (a separate launch so that the clear
-// kernel can read alloc while this one resets the sums)
-__global__ void k_oct_clear_ledger(OctState* st) {
-    st->block_iter_sum = 0;
-    for (int k = 0; k < kDepositStripes; ++k) st->deposits[k].v = 0;
+// The deposits of the call join their leaves' counts; those left at nodes
+// that have split since are part of the split.  Counters and queue lengths
+// return to zero for the next call.  One row of blocks per octree.
+__global__ void __launch_bounds__(256) k_oct_fold(int32_t* nodes, int32_t* fresh, const OctState* states,
+                                                  const OctParams* prm, const OctDyn* dyn, int32_t* cnt) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) cnt[1] = 0;
+    if (dyn->stop_filling) return;
+    const int32_t root = prm[blockIdx.y].root, n = min(states[blockIdx.y].alloc, prm[blockIdx.y].end) - root;
+    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+        const int32_t d = fresh[root + i];
+        if (d == 0) continue;
+        fresh[root + i] = 0;
+        const int32_t v = nodes[root + i];
+        if (v >= 0) nodes[root + i] = v + d;
+    }
 }
 
-__global__ void k_oct_clear_counter(int32_t* c) { *c = 0; }
+__global__ void k_oct_zero(int32_t* p, int64_t n) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += gridDim.x * (int64_t)blockDim.x)
+        p[i] = 0;
+}
 
 __global__ void k_oct_set_dyn(OctDyn* dyn, OctDyn d) { *dyn = d; }
 
@@ -470,21 +511,21 @@ void octree_dyn_for(OctDyn& d, int32_t iter) {
     d.split_count = kOctSplitFactor * ic;
 }
 
-hipError_t octree_insert_rounds(int32_t* nodes, OctState* states, const OctParams* prm, const OctDyn* dyn,
-                                const float* pos, int stride, const int32_t* scene_word, int shift,
+hipError_t octree_insert_rounds(int32_t* nodes, int32_t* fresh, OctState* states, const OctParams* prm, int n_trees,
+                                const OctDyn* dyn, const float* pos, int stride, const int32_t* scene_word, int shift,
                                 const int32_t* n_dev, int32_t n_host, int32_t* const defer[2], int32_t* cnt,
                                 hipStream_t s) {
-    hipLaunchKernelGGL(k_oct_clear_counter, dim3(1), dim3(1), 0, s, cnt + 1);
-    hipLaunchKernelGGL(k_oct_insert, dim3(grid_for(n_host, 256)), dim3(256), 0, s, nodes, states, prm, dyn, pos, stride,
-                       scene_word, shift, (const int32_t*)nullptr, n_dev, n_host, defer[0], cnt + 1, cnt + 2);
+    hipLaunchKernelGGL(k_oct_insert, dim3(grid_for(n_host, 256)), dim3(256), 0, s, nodes, fresh, states, prm, dyn, pos,
+                       stride, scene_word, shift, (const int32_t*)nullptr, n_dev, n_host, defer[0], cnt + 1, cnt + 2);
     for (int r = 1; r < kOctLaunchRounds; ++r) {
-        hipLaunchKernelGGL(k_oct_insert, dim3(std::min(grid_for(n_host, 256), 1024)), dim3(256), 0, s, nodes, states,
-                           prm, dyn, pos, stride, scene_word, shift, (const int32_t*)defer[(r - 1) & 1],
+        hipLaunchKernelGGL(k_oct_insert, dim3(std::min(grid_for(n_host, 256), 1024)), dim3(256), 0, s, nodes, fresh,
+                           states, prm, dyn, pos, stride, scene_word, shift, (const int32_t*)defer[(r - 1) & 1],
                            (const int32_t*)(cnt + (r % 3)), n_host, defer[r & 1], cnt + ((r + 1) % 3),
                            cnt + ((r + 2) % 3));
     }
-    hipLaunchKernelGGL(k_oct_insert_tail, dim3(1), dim3(256), 0, s, nodes, states, prm, dyn, pos, stride, scene_word,
-                       shift, defer[0], defer[1], cnt, n_host);
+    hipLaunchKernelGGL(k_oct_insert_tail, dim3(1), dim3(256), 0, s, nodes, fresh, states, prm, dyn, pos, stride,
+                       scene_word, shift, defer[0], defer[1], cnt, n_host);
+    hipLaunchKernelGGL(k_oct_fold, dim3(512, n_trees), dim3(256), 0, s, nodes, fresh, states, prm, dyn, cnt);
     return hipGetLastError();
 }
 
@@ -512,9 +553,18 @@ hipError_t octree_set_dyn(OctDyn* dyn, const OctDyn& d, hipStream_t s) {
 // ---------------------------------------------------------------------------
 // standalone octree: one octree, root 0, params copied to the device
 // ---------------------------------------------------------------------------
-hipError_t octree_reserve(Octree& o, int64_t n) {
+hipError_t octree_reserve(Octree& o, int64_t n, hipStream_t s) {
     hipError_t e = hipSuccess;
-    if (!o.defer_cnt) e = hipMalloc(&o.defer_cnt, 4 * 3);
+    if (!o.defer_cnt) {
+        e = hipMalloc(&o.defer_cnt, 4 * 3);
+        if (e == hipSuccess) hipLaunchKernelGGL(k_oct_zero, dim3(1), dim3(64), 0, s, o.defer_cnt, (int64_t)3);
+    }
+    if (!o.fresh && e == hipSuccess) {
+        e = hipMalloc(&o.fresh, 4 * (size_t)o.capacity);
+        if (e == hipSuccess)
+            hipLaunchKernelGGL(k_oct_zero, dim3(grid_for(o.capacity, 256)), dim3(256), 0, s, o.fresh,
+                               (int64_t)o.capacity);
+    }
     if (e != hipSuccess || n <= o.defer_cap) return e;
     if (o.defer[0]) (void)hipFree(o.defer[0]);
     if (o.defer[1]) (void)hipFree(o.defer[1]);
@@ -530,6 +580,7 @@ void octree_release(Octree& o) {
     if (o.defer[0]) (void)hipFree(o.defer[0]);
     if (o.defer[1]) (void)hipFree(o.defer[1]);
     if (o.defer_cnt) (void)hipFree(o.defer_cnt);
+    if (o.fresh) (void)hipFree(o.fresh);
     if (o.nodes) (void)hipFree(o.nodes);
     if (o.state) (void)hipFree(o.state);
     if (o.dyn) (void)hipFree(o.dyn);
@@ -548,10 +599,10 @@ hipError_t octree_reset(Octree& o, hipStream_t s) {
 hipError_t octree_increment_xyz(Octree& o, const float* pos, int32_t n, int single, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     if (single) return octree_insert_single(o.nodes, o.state, o.prm_dev, o.dyn, pos, 3, nullptr, 0, nullptr, n, s);
-    hipError_t e = octree_reserve(o, n);
+    hipError_t e = octree_reserve(o, n, s);
     if (e != hipSuccess) return e;
-    return octree_insert_rounds(o.nodes, o.state, o.prm_dev, o.dyn, pos, 3, nullptr, 0, nullptr, n, o.defer,
-                                o.defer_cnt, s);
+    return octree_insert_rounds(o.nodes, o.fresh, o.state, o.prm_dev, 1, o.dyn, pos, 3, nullptr, 0, nullptr, n,
+                                o.defer, o.defer_cnt, s);
 }
 
 hipError_t octree_density_raw(const int32_t* nodes, const OctState* st, const OctParams& P, const OctDyn* dyn,
@@ -570,7 +621,6 @@ hipError_t octree_density_xyz(const Octree& o, const float* pos, const float* nr
 hipError_t octree_clear(const Octree& o, hipStream_t s) {
     hipLaunchKernelGGL(k_oct_clear, dim3(grid_for(o.capacity, 256)), dim3(256), 0, s, o.nodes, o.state, o.prm.root,
                        o.prm.end);
-    hipLaunchKernelGGL(k_oct_clear_ledger, dim3(1), dim3(1), 0, s, o.state);
     return hipGetLastError();
 }
 

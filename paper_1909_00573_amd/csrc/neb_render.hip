@@ -2123,6 +2123,7 @@ struct neb_ctx_s {
     std::vector<void*> scene_allocs;
     // octree pool: scene s owns [oct_prm[s].root, oct_prm[s].end)
     int32_t* oct_nodes = nullptr;
+    int32_t* oct_fresh = nullptr;  // deposits of the iteration in progress, 0 between iterations
     OctState* oct_states = nullptr;
     OctParams* oct_prm_dev = nullptr;
     OctDyn* oct_dyn = nullptr;
@@ -2571,6 +2572,7 @@ extern "C" neb_status neb_create_batch(const neb_params* params, int32_t n_scene
     ALLOC(c->img, 12 * npix);
     ALLOC(c->cnt, 1);
     ALLOC(c->oct_nodes, oct_total);
+    ALLOC(c->oct_fresh, oct_total);
     ALLOC(c->oct_states, n_scenes);
     ALLOC(c->oct_prm_dev, n_scenes);
     ALLOC(c->oct_dyn, 1);
@@ -2615,6 +2617,8 @@ extern "C" neb_status neb_create_batch(const neb_params* params, int32_t n_scene
         if (c->ng.count)
             hipLaunchKernelGGL(k_fill_i32, dim3(grid_of((int64_t)c->ng.T + 1, 256)), dim3(256), 0, nullptr, c->ng.count,
                                0, (int64_t)c->ng.T + 1);
+        hipLaunchKernelGGL(k_fill_i32, dim3(grid_of(oct_total, 256)), dim3(256), 0, nullptr, c->oct_fresh, 0, oct_total);
+        hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, nullptr, c->defer_cnt, 0, (int64_t)3);
         hipLaunchKernelGGL(k_fill_i32, dim3(grid_of(c->n_bins + 2, 256)), dim3(256), 0, nullptr, c->bcount, 0,
                            (int64_t)c->n_bins + 2);
         hipLaunchKernelGGL(k_fill_f32, dim3(grid_of(12 * npix, 256)), dim3(256), 0, nullptr, c->img, 0.f, 12 * npix);
@@ -3226,7 +3230,8 @@ static neb_status enqueue_iteration(neb_ctx c, hipStream_t s, int parity, bool c
             e = octree_insert_single(c->oct_nodes, c->oct_states, c->oct_prm_dev, c->oct_dyn, pos, 4, tagw, 8, c->slots,
                                      (int32_t)c->slot_cap, s);
         else
-            e = octree_insert_rounds(c->oct_nodes, c->oct_states, c->oct_prm_dev, c->oct_dyn, pos, 4, tagw, 8,
+            e = octree_insert_rounds(c->oct_nodes, c->oct_fresh, c->oct_states, c->oct_prm_dev, c->n_scenes, c->oct_dyn,
+                                     pos, 4, tagw, 8,
                                      nv, (int32_t)vcap, c->defer, c->defer_cnt, s);
         prof_end(c, s);
         HIP_TRY(e);
