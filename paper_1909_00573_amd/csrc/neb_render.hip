@@ -142,6 +142,7 @@ struct DGrid {
     int32_t* start;   // T + 1 entries
     float4* pts;      // (pos, scene) in bucket order
     int32_t* vidx;    // vertex index of each entry (the vertices' grids)
+    int32_t* rank;    // per vertex: its place in its bucket (the vertices' grids)
     int32_t* sums;    // scan block sums
     int32_t T;        // buckets (power of two)
 };
@@ -267,6 +268,48 @@ __global__ void k_mean_image(const float* e, const float* E, const float* P, con
 __global__ void k_scale_image(const float* a, float* out, int64_t n, float scale) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         out[i] = a[i] * scale;
+}
+
+// A value loaded where this stands, together with what is loaded around it.
+// The compiler moves a load into the branch that uses it, and a record read
+// piece by piece then costs one round trip after another: the merge grid's
+// scatter read a vertex in four, a scattering photon its material in three.
+// Alone, per iteration: merge grid of the room 279 -> 216 us, of the city 537
+// -> 440, of ten box rooms 508 -> 415; photon scatter of the room 283 -> 267,
+// shading 158 -> 153.  (The merges, bound by the lines they ask for, gain
+// nothing: 2.22 ms either way.)
+__device__ __forceinline__ void here(float& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void here(int& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void here(float4& v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
+
+// what scattering at a surface needs of a material
+__device__ __forceinline__ neb_material load_scatter(const neb_material* m) {
+    neb_material r{};
+    r.type = m->type;
+    r.albedo[0] = m->albedo[0];
+    r.albedo[1] = m->albedo[1];
+    r.albedo[2] = m->albedo[2];
+    r.ior = m->ior;
+    r.alpha = m->alpha;
+    here(r.type);
+    here(r.albedo[0]);
+    here(r.albedo[1]);
+    here(r.albedo[2]);
+    here(r.ior);
+    here(r.alpha);
+    return r;
+}
+// ... and its emission
+__device__ __forceinline__ neb_material load_material(const neb_material* m) {
+    float e0 = m->emission[0], e1 = m->emission[1], e2 = m->emission[2];
+    neb_material r = load_scatter(m);
+    here(e0);
+    here(e1);
+    here(e2);
+    r.emission[0] = e0;
+    r.emission[1] = e1;
+    r.emission[2] = e2;
+    return r;
 }
 
 // ---------------------------------------------------------------------------
@@ -576,7 +619,7 @@ __global__ void __launch_bounds__(kShadeBlock) k_shade(RenderArgs A, PathQ in, c
         float4 pn = alive ? S.prim_n[prim] : make_float4(0.f, 0.f, 1.f, 0.f);
         f3 nrm = xyz(pn);
         int mid = fbits(pn.w);
-        const neb_material& m = S.mats[alive ? mid : 0];
+        const neb_material m = load_material(S.mats + (alive ? mid : 0));
         f3 wo = -d;
         float cin = dot3(nrm, wo);
         if (alive && rc) {
@@ -802,8 +845,10 @@ __device__ __forceinline__ float point_density(const RenderArgs& A, int s, f3 x,
     return oct_query_robust(nodes, prm[s], scale, ost[s].depth, x, nn);
 }
 
-// density grid over this iteration's NEE vertices: count -> scan -> scatter
-// (count returns to zero after the scatter)
+// density grid over this iteration's NEE vertices, built as the merge grid is:
+// the count keeps each vertex's place in its bucket, so that only one of the
+// two passes waits for returning atomics (about 25 G/s): alone, per iteration,
+// city (3.6 M vertices) 457 -> 385 us, ten box rooms 454 -> 365 us.
 // (recycling = 1: the cells of the NEE recycling radius)
 __global__ void __launch_bounds__(256) k_dgrid_count(const SceneInfo* sc, VertexStore V, const int32_t* n_vertices,
                                                      DGrid D, int recycling) {
@@ -811,7 +856,7 @@ __global__ void __launch_bounds__(256) k_dgrid_count(const SceneInfo* sc, Vertex
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         const int s = tag_scene(fbits(V.v1[i].w));
         const float inv = recycling ? sc[s].inv_ncell : sc[s].inv_dcell;
-        atomicAdd(&D.count[point_hash(xyz(V.v0[i]), inv, s, D.T)], 1);
+        D.rank[i] = atomicAdd(&D.count[point_hash(xyz(V.v0[i]), inv, s, D.T)], 1);
     }
 }
 __global__ void __launch_bounds__(256) k_dgrid_scatter(const SceneInfo* sc, VertexStore V, const int32_t* n_vertices,
@@ -820,8 +865,10 @@ __global__ void __launch_bounds__(256) k_dgrid_scatter(const SceneInfo* sc, Vert
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         const int s = tag_scene(fbits(V.v1[i].w));
         const f3 p = xyz(V.v0[i]);
+        int rank = D.rank[i];
+        here(rank);
         const uint32_t h = point_hash(p, recycling ? sc[s].inv_ncell : sc[s].inv_dcell, s, D.T);
-        const int pos = D.start[h] + atomicSub(&D.count[h], 1) - 1;
+        const int pos = D.start[h] + rank;
         D.pts[pos] = f4(p, ibits(s));
         D.vidx[pos] = i;
     }
@@ -945,7 +992,12 @@ __device__ __forceinline__ LightSample sample_light(const SceneView& S, int base
     ls.cos_l = 0.f;
     ls.lid = pick_light(S, base, count, u.u[0]);
     const float4* L = S.lights + 5 * (size_t)ls.lid;
-    float4 l0 = L[0], l1 = L[1], l2 = L[2], l3 = L[3];
+    float4 l0 = L[0], l1 = L[1], l2 = L[2], l3 = L[3], l4 = L[4];
+    here(l0);
+    here(l1);
+    here(l2);
+    here(l3);
+    here(l4);
     float psel = l0.w;
     if (l1.w > 0.f) {  // emissive triangle
         float su = sqrtf(u.u[1]);
@@ -955,7 +1007,7 @@ __device__ __forceinline__ LightSample sample_light(const SceneView& S, int base
         f3 dv = y - x;
         float d2 = dot3(dv, dv);
         f3 w = dv * rsqrtf(d2);
-        f3 ln = xyz(L[4]);
+        f3 ln = xyz(l4);
         ls.x = y;
         ls.n = ln;
         ls.w = w;
@@ -1058,12 +1110,16 @@ __global__ void __launch_bounds__(kNeeBlock) k_nee_finish(RenderArgs A, VertexSt
         s.ev = 0;
         float4 a0 = make_float4(0.f, 0.f, 0.f, 0.f), a1 = a0, a2 = a0, a3 = a0;
         float rho = 0.f;
+        int seen = 0;
         if (valid) {
             a0 = V.v0[i];
             a1 = V.v1[i];
             a2 = V.v2[i];
             a3 = V.v3[i];
             rho = V.rho[i];
+            seen = visible[i];
+            here(rho);
+            here(seen);
         }
         f3 x = xyz(a0), nrm = xyz(a1), wo = xyz(a2), tau = xyz(a3);
         int pixel = fbits(a0.w);
@@ -1079,7 +1135,7 @@ __global__ void __launch_bounds__(kNeeBlock) k_nee_finish(RenderArgs A, VertexSt
         if (valid) {
             U4 u = uniforms(I.k0, I.k1, lpix, (uint32_t)iter, (uint32_t)k, kTagNee);
             ls = sample_light(S, I.light_base, I.n_lights, x, nrm, u);
-            const bool ok = !is_zero3(ls.dE) && visible[i] != 0;
+            const bool ok = !is_zero3(ls.dE) && seen != 0;
             // NEE recycling: the sample is kept for the neighbours, L_E comes later
             if (A.recycle) V.lsrec[i] = f4(ls.x, ibits(ok ? ls.lid : -1));
             if (ok) {
@@ -1330,10 +1386,12 @@ __global__ void __launch_bounds__(256) k_grid_count(const neb_material* mats, co
                                                     const int32_t* n_vertices, Grid G) {
     int n = *n_vertices;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+        float4 a0 = V.v0[i];
         int tg = fbits(V.v1[i].w);
+        here(a0);
         if (mat_delta(mats[tag_mat(tg)].type)) continue;
         int s = tag_scene(tg);
-        G.rank[i] = atomicAdd(&G.count[grid_key(G, point_hash(xyz(V.v0[i]), sc[s].inv_cell, s, G.T), tag_depth(tg))], 1);
+        G.rank[i] = atomicAdd(&G.count[grid_key(G, point_hash(xyz(a0), sc[s].inv_cell, s, G.T), tag_depth(tg))], 1);
     }
 }
 
@@ -1341,19 +1399,24 @@ __global__ void __launch_bounds__(256) k_grid_scatter(const neb_material* mats, 
                                                       const int32_t* n_vertices, Grid G) {
     int n = *n_vertices;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        float4 a1 = V.v1[i];
+        float4 a1 = V.v1[i], a0 = V.v0[i], a2 = V.v2[i], a3 = V.v3[i];
+        int rank = G.rank[i];  // (not written for a specular vertex)
+        here(a0);
+        here(a1);
+        here(a2);
+        here(a3);
+        here(rank);
         int tg = fbits(a1.w);
         if (mat_delta(mats[tag_mat(tg)].type)) continue;
         int s = tag_scene(tg);
-        float4 a0 = V.v0[i];
         f3 p = xyz(a0);
         int64_t key = grid_key(G, point_hash(p, sc[s].inv_cell, s, G.T), tag_depth(tg));
-        int pos = G.start[key] + G.rank[i];
+        int pos = G.start[key] + rank;
         G.sorted[pos] = f4(p, ibits(s | (tag_depth(tg) << 24)));
         float4* m = G.mrec + 4 * (size_t)pos;
         m[0] = a1;
-        m[1] = V.v2[i];
-        m[2] = V.v3[i];
+        m[1] = a2;
+        m[2] = a3;
         m[3] = make_float4(a0.w, 0.f, 0.f, 0.f);
     }
 }
@@ -1832,10 +1895,16 @@ __global__ void __launch_bounds__(kScatterBlock) k_pscatter(RenderArgs A, Photon
         bool go = false;
         float4 r0 = make_float4(0.f, 0.f, 0.f, 0.f), r1 = r0, r2 = r0;
         float Un = 0.f;
-        const int2 h = i < n ? hits[i] : make_int2(0, -1);
-        if (h.y >= 0) {
-            const float4 b0 = in.p0[i], b1 = in.p1[i], b2 = in.p2[i];
-            const float U = in.pu[i];
+        // the whole photon beside its hit (past the end: the block's first one)
+        const int il = i < n ? i : base;
+        int2 h = hits[il];
+        float4 b0 = in.p0[il], b1 = in.p1[il], b2 = in.p2[il];
+        float U = in.pu[il];
+        here(b0);
+        here(b1);
+        here(b2);
+        here(U);
+        if (i < n && h.y >= 0) {
             const int tg = fbits(b1.w);
             const int code = tag_depth(tg), sid = tag_scene(tg);
             const int j = code & 15, odepth = code >> 4, opix = fbits(b0.w);
@@ -1844,7 +1913,7 @@ __global__ void __launch_bounds__(kScatterBlock) k_pscatter(RenderArgs A, Photon
             const f3 y = xyz(b0) + d * ibits(h.x);
             const float4 pn = S.prim_n[h.y];
             const f3 ny = xyz(pn);
-            const neb_material& my = S.mats[fbits(pn.w)];
+            const neb_material my = load_scatter(S.mats + fbits(pn.w));
             if (j < I.L - 2 && !mat_black(my)) {
                 // a light photon at its first hit brings the weight of its own
                 // technique in p2.w and X in U; every other photon has weight 1
@@ -2532,6 +2601,7 @@ extern "C" neb_status neb_create_batch(const neb_params* params, int32_t n_scene
     // Two depth classes and about as many buckets as vertices: a cell's row
     // is 8 bytes, so that the 2 x 2 x 2 cells of a Morton octet lie in one
     // 64-byte sector.  With eight classes of half as many buckets the table
+        ALLOC(c->ng.rank, vcap);
     // was twice as large (four classes: as large) and a hit's lookups spread
     // over more lines; fewer candidates did not make up for it.  Merges per
     // iteration, room / 12 x 12-lot city / batch, us: eight 1615 / 520 / 695,
@@ -2544,6 +2614,7 @@ extern "C" neb_status neb_create_batch(const neb_params* params, int32_t n_scene
     const int32_t half = (int32_t)std::max<uint64_t>(1024, std::min<uint64_t>(around / 2, 1u << 23));
     int64_t gkeys = (int64_t)c->G.T * c->G.D + 1;
     ALLOC(c->G.count, gkeys);
+        ALLOC(c->dg.rank, vcap);
     ALLOC(c->G.start, gkeys);
     ALLOC(c->G.rank, vcap);
     ALLOC(c->G.sorted, vcap);
@@ -3217,7 +3288,7 @@ static neb_status enqueue_iteration(neb_ctx c, hipStream_t s, int parity, bool c
         prof_begin(c, K_DENSITY_GRID, s);
         hipLaunchKernelGGL(k_dgrid_count, dim3(grid_of(vcap, 256)), dim3(256), 0, s, (const SceneInfo*)c->sc_dev, c->V,
                            (const int32_t*)nv, c->dg, 0);
-        scan_exclusive(c->dg.count, c->dg.start, (int64_t)c->dg.T + 1, c->dg.sums, s);
+        scan_exclusive(c->dg.count, c->dg.start, (int64_t)c->dg.T + 1, c->dg.sums, s, true);
         hipLaunchKernelGGL(k_dgrid_scatter, dim3(grid_of(vcap, 256)), dim3(256), 0, s, (const SceneInfo*)c->sc_dev,
                            c->V, (const int32_t*)nv, c->dg, 0);
         prof_end(c, s);
@@ -3278,7 +3349,7 @@ static neb_status enqueue_iteration(neb_ctx c, hipStream_t s, int parity, bool c
         prof_begin(c, K_NEE_RECYCLE, s);
         hipLaunchKernelGGL(k_dgrid_count, dim3(grid_of(vcap, 256)), dim3(256), 0, s, (const SceneInfo*)c->sc_dev, c->V,
                            (const int32_t*)nv, c->ng, 1);
-        scan_exclusive(c->ng.count, c->ng.start, (int64_t)c->ng.T + 1, c->ng.sums, s);
+        scan_exclusive(c->ng.count, c->ng.start, (int64_t)c->ng.T + 1, c->ng.sums, s, true);
         hipLaunchKernelGGL(k_dgrid_scatter, dim3(grid_of(vcap, 256)), dim3(256), 0, s, (const SceneInfo*)c->sc_dev,
                            c->V, (const int32_t*)nv, c->ng, 1);
         hipLaunchKernelGGL(k_nee_count, dim3(grid_of(vcap, 256)), dim3(256), 0, s, A, c->V,
