@@ -382,8 +382,8 @@ __device__ __forceinline__ int hit_bin(const HitBins& B, int scene, f3 y) {
 // closest hit for a queue of rays given as (origin, direction) float4 arrays
 // (the direction's w is a tag word naming the scene); also clears the
 // counter of the queue the next kernel appends to (if any).  kAnyHit: shadow
-// rays, each ending at tmax[i]; vis[origin's w word] gets 1 if nothing is
-// hit before it, else 0 (no hits are written).  ray_kind names the statistic
+// rays, each ending at tmax[i]; vis[origin's w word] gets -1 if something is
+// hit before it (no hits are written).  ray_kind names the statistic
 // the rays count in: 0 camera, 1 photon, 2 shadow rays.  Optionally counts
 // the hits per spatial bin.  Off: byte offsets into the node and triangle
 // pools (32 bits unless a pool reaches 4 GB).
@@ -459,7 +459,7 @@ __global__ void __launch_bounds__(kTraceBlock) k_extend(SceneView S, const Scene
     };
     auto finish = [&]() {
         if (kAnyHit) {
-            vis[fbits(org[i].w)] = T.prim < 0 ? 1 : 0;
+            if (T.prim >= 0) vis[fbits(org[i].w)] = -1;
         } else {
             hits[i] = make_int2(fbits(T.best), T.prim);
             if (B.bin) {
@@ -983,15 +983,15 @@ __device__ __forceinline__ float emission_density(bool area, float cos_l, float 
     return (area ? fmaxf(cos_l, 0.f) * (1.0f / NEB_PI) : 1.0f / (4.0f * NEB_PI)) * cx / d2;
 }
 
-__device__ __forceinline__ LightSample sample_light(const SceneView& S, int base, int count, f3 x, f3 nx,
-                                                    const U4& u) {
+// the sample of light lid (pick_light's) seen from x
+__device__ __forceinline__ LightSample sample_light(const SceneView& S, int lid, f3 x, f3 nx, const U4& u) {
     LightSample ls;
     ls.dE = mk3(0.f, 0.f, 0.f);
     ls.hittable = false;
     ls.p_light = 0.f;
     ls.cos_l = 0.f;
-    ls.lid = pick_light(S, base, count, u.u[0]);
-    const float4* L = S.lights + 5 * (size_t)ls.lid;
+    ls.lid = lid;
+    const float4* L = S.lights + 5 * (size_t)lid;
     float4 l0 = L[0], l1 = L[1], l2 = L[2], l3 = L[3], l4 = L[4];
     here(l0);
     here(l1);
@@ -1035,16 +1035,21 @@ __device__ __forceinline__ LightSample sample_light(const SceneView& S, int base
 }
 
 // NEE (Sec. 3.1) in three launches over the vertices: k_nee_rays draws each
-// vertex's light sample and queues a shadow ray where the sample carries
-// energy (slots reserved once per block of 512 threads); a closest-hit launch in
+// vertex's light sample, queues a shadow ray where the sample carries
+// energy and notes its light (-1: no energy) (slots reserved once per block of 512 threads); a closest-hit launch in
 // any-hit mode traces the queue (a lane takes the next ray when its own
-// ends, so vertices without a ray leave no lane idle during traversal);
-// k_nee_finish draws the same sample again (same stream), adds L_E and emits
-// the NEB photon of every visible vertex.
+// ends, so vertices without a ray leave no lane idle during traversal) and
+// marks the hidden ones -1 too; k_nee_finish draws the same point of the noted
+// light again (same stream), adds L_E and emits the NEB photon of every visible vertex.
+// It is bound by the latency of its chain of loads: picking the light again
+// (guide, cumulative table, then the light) and drawing for hidden vertices too,
+// all three NEE launches took, alone, city 1.00 ms (now 0.91), ten box rooms
+// 0.56 (0.51), room 0.37 (0.36).
 constexpr int kNeeBlock = 512;
 __global__ void __launch_bounds__(kNeeBlock) k_nee_rays(RenderArgs A, VertexStore V, const int32_t* n_vertices,
                                                         float4* __restrict__ s0, float4* __restrict__ s1,
-                                                        float* __restrict__ stmax, int32_t* n_shadow) {
+                                                        float* __restrict__ stmax, int32_t* n_shadow,
+                                                        int32_t* __restrict__ chosen) {
     __shared__ int wc[kNeeBlock / 64];
     __shared__ int bb;
     const int n = *n_vertices;
@@ -1064,8 +1069,9 @@ __global__ void __launch_bounds__(kNeeBlock) k_nee_rays(RenderArgs A, VertexStor
             sid = tag_scene(tg);
             const SceneInfo& I = A.sc[sid];
             U4 u = uniforms(I.k0, I.k1, (uint32_t)(pixel - I.pix_base), (uint32_t)iter, (uint32_t)k, kTagNee);
-            LightSample ls = sample_light(S, I.light_base, I.n_lights, x, nrm, u);
+            LightSample ls = sample_light(S, pick_light(S, I.light_base, I.n_lights, u.u[0]), x, nrm, u);
             ray = !is_zero3(ls.dE);
+            chosen[i] = ray ? ls.lid : -1;
             if (ray) {
                 so = offset_origin(x, nrm, ls.w, I.eps);
                 // An area light's sample point, rounded to floats, can sit a
@@ -1090,10 +1096,9 @@ __global__ void __launch_bounds__(kNeeBlock) k_nee_rays(RenderArgs A, VertexStor
     }
 }
 
-// vis[i]: 1 if vertex i's shadow ray reached the light (read only where the
-// sample carries energy, i.e. where k_nee_rays queued a ray)
+// chosen[i]: the light that vertex i's sample reaches, or -1
 __global__ void __launch_bounds__(kNeeBlock) k_nee_finish(RenderArgs A, VertexStore V, const int32_t* n_vertices,
-                                                          const int32_t* __restrict__ visible, Images img,
+                                                          const int32_t* __restrict__ chosen, Images img,
                                                           PhotonQ pq, int32_t* pcount) {
     __shared__ int wc[kNeeBlock / 64];
     __shared__ int bb;
@@ -1110,16 +1115,16 @@ __global__ void __launch_bounds__(kNeeBlock) k_nee_finish(RenderArgs A, VertexSt
         s.ev = 0;
         float4 a0 = make_float4(0.f, 0.f, 0.f, 0.f), a1 = a0, a2 = a0, a3 = a0;
         float rho = 0.f;
-        int seen = 0;
+        int lid = -1;
         if (valid) {
             a0 = V.v0[i];
             a1 = V.v1[i];
             a2 = V.v2[i];
             a3 = V.v3[i];
             rho = V.rho[i];
-            seen = visible[i];
+            lid = chosen[i];
             here(rho);
-            here(seen);
+            here(lid);
         }
         f3 x = xyz(a0), nrm = xyz(a1), wo = xyz(a2), tau = xyz(a3);
         int pixel = fbits(a0.w);
@@ -1132,12 +1137,12 @@ __global__ void __launch_bounds__(kNeeBlock) k_nee_finish(RenderArgs A, VertexSt
         ls.dE = mk3(0.f, 0.f, 0.f);
         // light photons: emission density p_{l -> l-1} from the light point toward x
         float rem = 0.f;
-        if (valid) {
+        if (lid >= 0) {
             U4 u = uniforms(I.k0, I.k1, lpix, (uint32_t)iter, (uint32_t)k, kTagNee);
-            ls = sample_light(S, I.light_base, I.n_lights, x, nrm, u);
-            const bool ok = !is_zero3(ls.dE) && seen != 0;
+            ls = sample_light(S, lid, x, nrm, u);
+            const bool ok = !is_zero3(ls.dE);
             // NEE recycling: the sample is kept for the neighbours, L_E comes later
-            if (A.recycle) V.lsrec[i] = f4(ls.x, ibits(ok ? ls.lid : -1));
+            if (A.recycle) V.lsrec[i] = f4(ls.x, ibits(ok ? lid : -1));
             if (ok) {
                 ++vis;
                 rem = emission_density(ls.hittable, ls.cos_l, fabsf(dot3(nrm, ls.w)), ls.d2);
@@ -1162,6 +1167,8 @@ __global__ void __launch_bounds__(kNeeBlock) k_nee_finish(RenderArgs A, VertexSt
                     photon = s.ev != 0;
                 }
             }
+        } else if (valid && A.recycle) {
+            V.lsrec[i] = make_float4(0.f, 0.f, 0.f, ibits(-1));
         }
         const int slot = block_reserve<kNeeBlock / 64>(pcount, photon, wc, &bb);
         if (photon) {
@@ -2192,7 +2199,7 @@ struct neb_ctx_s {
     int2* phits[kPhotonBufs]{};  // hit arrays of the photon queues (the first is hits)
     float4 *sq0 = nullptr, *sq1 = nullptr;  // NEE shadow rays: (origin, vertex), (direction, tag)
     float* sqt = nullptr;                   // their tmax
-    int32_t* svis = nullptr;                // per vertex: 1 if its shadow ray reached the light
+    int32_t* svis = nullptr;                // per vertex: the light its NEE sample reaches, or -1
     int2* hits = nullptr;
     // Two vertex and event stores, by the parity of the iteration: the
     // camera pass of the next iteration (on a third stream, cam) fills one
@@ -3138,7 +3145,7 @@ static void extend(neb_ctx c, int64_t cap, const float4* org, const float4* dir,
 static void nee_rays(neb_ctx c, const RenderArgs& A, hipStream_t s) {
     const int grid = grid_of(c->vcap, kNeeBlock);
     hipLaunchKernelGGL(k_nee_rays, dim3(grid), dim3(kNeeBlock), 0, s, A, c->V, (const int32_t*)c->nvtx,
-                       c->sq0, c->sq1, c->sqt, &c->cnt->n_shadow);
+                       c->sq0, c->sq1, c->sqt, &c->cnt->n_shadow, c->svis);
     if (c->cfg.stack == 32) launch_shadow<32>(c, s);
     else if (c->cfg.stack == 48) launch_shadow<48>(c, s);
     else launch_shadow<64>(c, s);
