@@ -400,7 +400,8 @@ __device__ __forceinline__ int hit_bin(const HitBins& B, int scene, f3 y) {
 // Alone, per iteration: city camera rays 7.17 -> 2.47 ms, photon rays 5.68 ->
 // 1.90 ms; room (512 x 512) camera rays 0.92 -> 0.60 ms, photon rays 1.45 ->
 // 0.90 ms, against a kernel that tested leaves where it met them.
-template <int kStack, bool kAnyHit, typename Off>
+constexpr int kDealRays = 16;
+template <int kStack, bool kAnyHit, typename Off, bool kDeal>
 __global__ void __launch_bounds__(kTraceBlock) k_extend(SceneView S, const SceneInfo* sc,
                                                         const float4* __restrict__ org,
                                                         const float4* __restrict__ dir, const int32_t* count,
@@ -471,12 +472,23 @@ __global__ void __launch_bounds__(kTraceBlock) k_extend(SceneView S, const Scene
         }
         ++traced;
     };
+    // A queue of at most kDealRays rays per wave of the launch is dealt out at
+    // once (kDeal), and the walk starts with the sharing below: a wave of 64 grazing
+    // rays has no lane free to help while other SIMDs have no wave at all.
+    // Each XCD takes a contiguous part.  (deals_rays has the figures.)
+    const bool dealt = kDeal && n <= kDealRays * (int)gridDim.x;
+    const int per = (n + (int)gridDim.x - 1) / (int)gridDim.x;
+    const int w = gridDim.x & 7 ? (int)blockIdx.x
+                                : (int)(blockIdx.x & 7) * ((int)gridDim.x >> 3) + (int)(blockIdx.x >> 3);
     while (more) {
         if (__popcll(__builtin_amdgcn_ballot_w64(!on)) >= kRefill) {
-            const int got = wave_reserve(next, !on);
+            int64_t g = lane < per ? w * per + lane : n;
+            if (!dealt) {
+                const int got = wave_reserve(next, !on);
+                g = ((int64_t)(got / kChunk) * parts + part) * kChunk + got % kChunk;
+            }
             bool out = false;
             if (!on) {
-                const int64_t g = ((int64_t)(got / kChunk) * parts + part) * kChunk + got % kChunk;
                 out = g >= n;
                 if (!out) {
                     i = (int)g;
@@ -486,7 +498,7 @@ __global__ void __launch_bounds__(kTraceBlock) k_extend(SceneView S, const Scene
                     if (!on) finish();
                 }
             }
-            more = !__any(out);
+            more = !dealt && !__any(out);
         }
         if (step()) {
             finish();
@@ -559,7 +571,7 @@ __global__ void __launch_bounds__(kTraceBlock) k_extend(SceneView S, const Scene
     }
     // the last block to finish resets the work counter for the next launch
     __syncthreads();
-    if (threadIdx.x == 0 && atomicAdd(work_done, 1) == (int)gridDim.x - 1) {
+    if (!dealt && threadIdx.x == 0 && atomicAdd(work_done, 1) == (int)gridDim.x - 1) {
         for (int k = 0; k < kWorkParts; ++k) work[k].next = 0;
         *work_done = 0;
     }
@@ -2372,11 +2384,19 @@ static int lds_blocks_per_cu(int stack) { return (160 * 1024) / (stack * kTraceB
 
 // blocks of a traversal launch over a queue of at most cap rays, with bpc
 // blocks per CU (0: one block per 64 queue slots, -1: as many as the LDS holds)
+// Closest-hit launches deal short queues out in contexts of at most 65 536
+// pixels, whose queues leave most of the chip without a wave.  City of 120 x 120 lots at 160 x 120, two iterations:
+// 7.2 -> 2.6 ms; of 12 x 12 lots at 60 x 50 1.50 -> 0.66; 64 x 64 preview 1.29
+// -> 1.11.  Larger frames lose by it (waves with few rays beside the other
+// streams' kernels): 401 x 227 room 5.76 -> 5.83 ms, 1024 x 1024 city 12.33 -> 12.46.
+static bool deals_rays(neb_ctx c) { return c->npix <= 65536; }
 static int trace_grid(neb_ctx c, int64_t cap, int bpc) {
     if (bpc < 0 || bpc > lds_blocks_per_cu(c->cfg.stack)) bpc = lds_blocks_per_cu(c->cfg.stack);
-    // never more blocks than the queue has lanes' worth of rays: a small
-    // queue would leave most blocks without work
-    if (bpc > 0) return std::max(1, (int)std::min<int64_t>((int64_t)c->cus * bpc, (cap + kTraceBlock - 1) / kTraceBlock));
+    // never more blocks than the queue has lanes' worth of rays, or than
+    // leave a wave eight rays of it where the queue is dealt out (two: 60 x 50
+    // city 0.82 instead of 0.66 ms)
+    const int least = deals_rays(c) ? 8 : kTraceBlock;
+    if (bpc > 0) return std::max(1, (int)std::min<int64_t>((int64_t)c->cus * bpc, (cap + least - 1) / least));
     return grid_of(cap, kTraceBlock, 1 << 20);
 }
 
@@ -3091,10 +3111,10 @@ static RenderArgs make_args(neb_ctx c) {
 // 32-bit byte offsets hold for pools of at most 4 GB
 static bool small_pools(neb_ctx c) { return std::max(c->node_bytes, c->tri_bytes) <= (int64_t)UINT32_MAX; }
 
-template <int kStack, typename Off>
+template <int kStack, typename Off, bool kDeal>
 static void launch_extend_(neb_ctx c, int64_t cap, const float4* org, const float4* dir, int32_t* count, int32_t* next,
                           int rays, const HitBins& B, int2* hits, hipStream_t s) {
-    hipLaunchKernelGGL((k_extend<kStack, false, Off>), dim3(trace_grid(c, cap, c->cfg.trace_bpc)), dim3(kTraceBlock), 0, s,
+    hipLaunchKernelGGL((k_extend<kStack, false, Off, kDeal>), dim3(trace_grid(c, cap, c->cfg.trace_bpc)), dim3(kTraceBlock), 0, s,
                        c->view, (const SceneInfo*)c->sc_dev, org, dir, (const int32_t*)count, next, hits, rays,
                        c->cnt, B, (const float*)nullptr, (int32_t*)nullptr,
                        rays == 0 ? c->cnt->cam_next : c->cnt->trace_next,
@@ -3104,14 +3124,15 @@ static void launch_extend_(neb_ctx c, int64_t cap, const float4* org, const floa
 template <int kStack>
 static void launch_extend(neb_ctx c, int64_t cap, const float4* org, const float4* dir, int32_t* count, int32_t* next,
                           int rays, const HitBins& B, int2* hits, hipStream_t s) {
-    if (small_pools(c)) launch_extend_<kStack, uint32_t>(c, cap, org, dir, count, next, rays, B, hits, s);
-    else launch_extend_<kStack, uint64_t>(c, cap, org, dir, count, next, rays, B, hits, s);
+    if (!small_pools(c)) launch_extend_<kStack, uint64_t, false>(c, cap, org, dir, count, next, rays, B, hits, s);
+    else if (deals_rays(c)) launch_extend_<kStack, uint32_t, true>(c, cap, org, dir, count, next, rays, B, hits, s);
+    else launch_extend_<kStack, uint32_t, false>(c, cap, org, dir, count, next, rays, B, hits, s);
 }
 
 // the queued NEE shadow rays, any-hit, with the NEE launch shape
-template <int kStack, typename Off>
+template <int kStack, typename Off, bool kDeal>
 static void launch_shadow_(neb_ctx c, hipStream_t s) {
-    hipLaunchKernelGGL((k_extend<kStack, true, Off>), dim3(trace_grid(c, c->vcap, c->cfg.nee_bpc)), dim3(kTraceBlock), 0, s,
+    hipLaunchKernelGGL((k_extend<kStack, true, Off, kDeal>), dim3(trace_grid(c, c->vcap, c->cfg.nee_bpc)), dim3(kTraceBlock), 0, s,
                        c->view, (const SceneInfo*)c->sc_dev, (const float4*)c->sq0, (const float4*)c->sq1,
                        (const int32_t*)&c->cnt->n_shadow, (int32_t*)nullptr, (int2*)nullptr, 2, c->cnt, HitBins{},
                        (const float*)c->sqt, c->svis, c->cnt->trace_next, &c->cnt->trace_done);
@@ -3119,8 +3140,9 @@ static void launch_shadow_(neb_ctx c, hipStream_t s) {
 
 template <int kStack>
 static void launch_shadow(neb_ctx c, hipStream_t s) {
-    if (small_pools(c)) launch_shadow_<kStack, uint32_t>(c, s);
-    else launch_shadow_<kStack, uint64_t>(c, s);
+    if (!small_pools(c)) launch_shadow_<kStack, uint64_t, false>(c, s);
+    else if (deals_rays(c)) launch_shadow_<kStack, uint32_t, true>(c, s);
+    else launch_shadow_<kStack, uint32_t, false>(c, s);
 }
 
 // rays: 0 counts camera rays (the camera pass, which has work counters of
