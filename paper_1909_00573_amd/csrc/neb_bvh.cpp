@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <limits>
 #include <vector>
 
 namespace neb {
@@ -288,6 +289,48 @@ bool build_bvh(const float* vertices, int32_t nv, const int32_t* tris, int32_t n
     }
     out.n_nodes = n_dev;
     return tri_cursor == nt;
+}
+
+void bvh_device_layout(const BvhHost& B, int32_t node_base, int32_t tri_base, int32_t none, float* nodes, float* tris) {
+    for (size_t t = 0; t < B.tris.size() / 12; ++t) {
+        float* dst = tris + 12 * t;
+        std::memcpy(dst, &B.tris[12 * t], 48);
+        int32_t pid;
+        std::memcpy(&pid, dst + 3, 4);
+        pid += tri_base;
+        std::memcpy(dst + 3, &pid, 4);
+    }
+    for (int i = 0; i < B.n_nodes; ++i) {
+        float* dst = nodes + 32 * (size_t)i;
+        std::memcpy(dst, &B.nodes[32 * (size_t)i], 32 * 4);
+        int32_t ref[4], ct[4];
+        std::memcpy(ref, dst + 24, 16);
+        std::memcpy(ct, dst + 28, 16);
+        for (int c = 0; c < 4; ++c) {
+            if (ct[c] > 0) {
+                const int32_t last = 1;
+                std::memcpy(tris + 12 * (size_t)(ref[c] + ct[c] - 1) + 7, &last, 4);
+                ref[c] = ~(ref[c] + tri_base);
+            } else if (ref[c] >= 0) {
+                ref[c] += node_base;
+            } else {
+                // out of reach of any ray that the planes can tell apart
+                for (int a = 0; a < 3; ++a) {
+                    dst[4 * a + c] = 1e30f;
+                    dst[12 + 4 * a + c] = -1e30f;
+                }
+                ref[c] = ~none;
+            }
+        }
+        std::memcpy(dst + 24, ref, 16);
+    }
+}
+
+void bvh_no_triangle(float* tri) {
+    std::fill(tri, tri + 12, std::numeric_limits<float>::quiet_NaN());
+    const int32_t id = -1, last = 1;
+    std::memcpy(tri + 3, &id, 4);
+    std::memcpy(tri + 7, &last, 4);
 }
 
 }  // namespace neb

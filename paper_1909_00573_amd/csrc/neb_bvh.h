@@ -21,6 +21,18 @@ struct BvhHost {
 
 bool build_bvh(const float* vertices, int32_t nv, const int32_t* tris, int32_t nt, BvhHost& out);
 
-constexpr int32_t kBvhEmpty = 0x7FFFFFFF;  // device nodes: no child in this slot
+// The layout the device walks.  Every child is a reference: a node, or ~ the
+// first triangle of a leaf (the last triangle of a leaf is marked in its
+// second vertex's w).  An empty slot is a leaf too: the pool's one triangle
+// without a hit, number `none`.  So whatever a ray's slabs say (far enough
+// from the scene every slab is one distance, that of a box the wrong way round
+// too), a walk only ever reads the pools.
+//
+// B's nodes and triangles to `nodes` and `tris`, which lie at node_base and
+// tri_base in the pools
+void bvh_device_layout(const BvhHost& B, int32_t node_base, int32_t tri_base, int32_t none, float* nodes, float* tris);
+// the triangle without a hit (NaN vertices, which no distance passes), the
+// last of its leaf
+void bvh_no_triangle(float* tri);
 
 }  // namespace neb

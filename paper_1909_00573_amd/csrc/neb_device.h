@@ -492,8 +492,8 @@ struct TraceState {
     uint32_t nx, ny, nz, fx, fy, fz;
     float best;
     int prim;
-    // the last visited node's children: references (a node, ~ a leaf's first
-    // triangle, kBvhEmpty) and the distance of an inner child in reach, -1
+    // the last visited node's children: references (a node or ~ a leaf's
+    // first triangle) and the distance of an inner child in reach, -1
     // for a leaf in reach whose triangles are still to test, else INFINITY
     int c0, c1, c2, c3;
     float d0, d1, d2, d3;
@@ -518,14 +518,15 @@ __device__ __forceinline__ void trace_at(TraceState& T, int from, int* stack) {
     T.top = T.bot = stack;
 }
 
-// false: a ray that cannot hit anything (a NaN among its numbers, or no
-// length), which the walk must not see: only there could it enter an empty slot
+// false: a ray that cannot hit anything (a NaN or an infinity among its
+// numbers, or no length) and is spared the walk
 __device__ __forceinline__ bool trace_begin(TraceState& T, int root, int* stack, f3 o, f3 d, float tmax = INFINITY) {
     T.r = ray_pre(o, d);
     T.best = tmax;
     T.prim = -1;
     trace_at(T, root, stack);
-    return tmax > 0.f && o.x + o.y + o.z + (d.x + d.y + d.z) == o.x + o.y + o.z + (d.x + d.y + d.z);
+    return tmax > 0.f && fabsf(o.x) < INFINITY && fabsf(o.y) < INFINITY && fabsf(o.z) < INFINITY &&
+           fabsf(d.x) < INFINITY && fabsf(d.y) < INFINITY && fabsf(d.z) < INFINITY;
 }
 
 // (distance, node) pair of a child still to visit; compare-exchange by distance
@@ -549,7 +550,9 @@ __device__ __forceinline__ float4 pool16(const float4* base, Off byte) {
 // One node step.  The near and far planes are loaded by the ray's direction
 // signs, so a slab needs no minimum and maximum of its two distances.  An
 // empty slot's planes lie the wrong way round (1e30 before -1e30), out of
-// every ray's reach.  Returns false when no node is left: the ray is done.
+// reach; a ray from so far off that both are one distance to it tests the
+// slot's triangle, which is never hit.  Returns false when no node is left:
+// the ray is done.
 template <typename Off>
 __device__ __forceinline__ bool trace_node(const SceneView& S, TraceState& T) {
     const RayPre& r = T.r;

@@ -88,8 +88,9 @@ struct CamParams {
 // read-only geometry and light pools shared by every scene of a context
 struct SceneView {
     const float4* bvh;         // 8 float4 per node: low x, y, z and high x, y, z planes of the four children, their
-                               // references (a node, ~ a leaf's first triangle or kBvhEmpty), unused; all scenes
-    const float4* tri;         // 3 float4 per triangle in leaf order; [0].w = global prim id bits, [1].w = 1 for a leaf's last
+                               // references (a node or ~ a leaf's first triangle), unused; all scenes (bvh_device_layout)
+    const float4* tri;         // 3 float4 per triangle in leaf order; [0].w = global prim id bits, [1].w = 1 for a leaf's last;
+                               // after all scenes' the one without a hit, which empty child slots hold
     const float4* prim_n;      // per prim: unit geometric normal, .w = global material id bits
     const int32_t* prim_light; // per prim: global light index or -1
     const neb_material* mats;

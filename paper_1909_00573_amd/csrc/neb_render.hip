@@ -2915,50 +2915,19 @@ static neb_status prepare(neb_ctx c) {
     if (n_mats > kMaxMaterials) return fail(NEB_ERR_CAPACITY, "more than 65536 materials over the batch");
     if (n_nodes * 8 > (int64_t)INT32_MAX || n_tris * 3 > (int64_t)INT32_MAX || n_lights * 5 > (int64_t)INT32_MAX)
         return fail(NEB_ERR_CAPACITY, "geometry pools over 2^31 entries");
-    std::vector<float> nodes(32 * (size_t)n_nodes), tri(12 * (size_t)n_tris), prim_n(4 * (size_t)n_tris),
+    // (one triangle more: the one that empty slots hold)
+    std::vector<float> nodes(32 * (size_t)n_nodes), tri(12 * ((size_t)n_tris + 1)), prim_n(4 * (size_t)n_tris),
         lights(20 * (size_t)n_lights), cdf((size_t)n_lights);
     std::vector<int32_t> guide((size_t)n_lights);
     std::vector<int32_t> prim_light((size_t)n_tris);
     std::vector<neb_material> mats((size_t)n_mats);
+    bvh_no_triangle(&tri[12 * (size_t)n_tris]);
     int64_t nb = 0, tb = 0, mb = 0, lb = 0;
     for (int s = 0; s < c->n_scenes; ++s) {
         const HostScene& H = c->hs[s];
         const neb_params& P = c->prm[s];
-        // nodes: a child is a node index, ~ a leaf's first triangle or empty;
-        // the last triangle of a leaf is marked in its second vertex's w
-        for (int i = 0; i < H.bvh.n_nodes; ++i) {
-            const float* src = &H.bvh.nodes[32 * (size_t)i];
-            float* dst = &nodes[32 * (size_t)(nb + i)];
-            std::memcpy(dst, src, 32 * 4);
-            int32_t ref[4], ct[4];
-            std::memcpy(ref, src + 24, 16);
-            std::memcpy(ct, src + 28, 16);
-            for (int ch = 0; ch < 4; ++ch) {
-                if (ct[ch] > 0) {
-                    const int32_t first = ref[ch] + (int32_t)tb, last = 1;
-                    std::memcpy(&tri[12 * (size_t)(first + ct[ch] - 1) + 7], &last, 4);
-                    ref[ch] = ~first;
-                } else if (ref[ch] >= 0) {
-                    ref[ch] += (int32_t)nb;
-                } else {
-                    for (int a = 0; a < 3; ++a) {
-                        dst[4 * a + ch] = 1e30f;
-                        dst[12 + 4 * a + ch] = -1e30f;
-                    }
-                    ref[ch] = kBvhEmpty;
-                }
-            }
-            std::memcpy(dst + 24, ref, 16);
-        }
+        bvh_device_layout(H.bvh, (int32_t)nb, (int32_t)tb, (int32_t)n_tris, &nodes[32 * (size_t)nb], &tri[12 * (size_t)tb]);
         for (int t = 0; t < H.nt; ++t) {
-            const float* src = &H.bvh.tris[12 * (size_t)t];
-            float* dst = &tri[12 * (size_t)(tb + t)];
-            std::memcpy(dst, src, 28);
-            std::memcpy(dst + 8, src + 8, 16);
-            int32_t pid;
-            std::memcpy(&pid, src + 3, 4);
-            pid += (int32_t)tb;
-            std::memcpy(dst + 3, &pid, 4);
             float* pn = &prim_n[4 * (size_t)(tb + t)];
             std::memcpy(pn, &H.prim_n[4 * (size_t)t], 16);
             int32_t mid;
@@ -3022,7 +2991,7 @@ static neb_status prepare(neb_ctx c) {
     int32_t* d_guide = nullptr;
     neb_material* d_mats = nullptr;
     hipError_t e = dalloc(c->scene_allocs, &d_nodes, 8 * (size_t)n_nodes);
-    if (e == hipSuccess) e = dalloc(c->scene_allocs, &d_tri, 3 * (size_t)n_tris);
+    if (e == hipSuccess) e = dalloc(c->scene_allocs, &d_tri, 3 * ((size_t)n_tris + 1));
     if (e == hipSuccess) e = dalloc(c->scene_allocs, &d_pn, (size_t)n_tris);
     if (e == hipSuccess) e = dalloc(c->scene_allocs, &d_pl, (size_t)n_tris);
     if (e == hipSuccess) e = dalloc(c->scene_allocs, &d_mats, (size_t)n_mats);
@@ -3050,7 +3019,7 @@ static neb_status prepare(neb_ctx c) {
     c->view.light_guide = d_guide;
     c->forest_depth = depth;
     c->node_bytes = 128 * n_nodes;
-    c->tri_bytes = 48 * n_tris;
+    c->tri_bytes = 48 * (n_tris + 1);
     // the shallowest stack that holds every tree's deepest descent
     if (c->cfg.stack <= depth) c->cfg.stack = depth < 32 ? 32 : (depth < 48 ? 48 : 64);
     neb_status st = restart(c, nullptr);
