@@ -628,6 +628,13 @@ __device__ __forceinline__ bool trace_triangle(const SceneView& S, TraceState& T
     return true;
 }
 
+// LDS written by some lanes of the wave, to be read by others: the
+// barrier alone orders no memory access for the compiler
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // device-wide counter add with one atomic per wave
 __device__ __forceinline__ void wave_add_u64(unsigned long long* dst, unsigned v) {
     unsigned long long s = v;

@@ -153,12 +153,6 @@ struct WaveGroups {
     int size[64];   // per leading lane: lanes of its group
 };
 
-// LDS written by some lanes of the wave, to be read by others
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // Wave-cooperative deposit of one point per lane (lanes may belong to
 // different octrees of the pool).  Each pass: every lane descends to a leaf;
 // lanes at the same leaf form a group, whose leader adds the group's size to

@@ -520,6 +520,7 @@ __global__ void __launch_bounds__(kTraceBlock) k_extend(SceneView S, const Scene
     };
     res[lane] = key();
     parts_of[lane] = 1;
+    wave_sync();
     for (;;) {
         const unsigned long long idle = __builtin_amdgcn_ballot_w64(!on);
         if (!~idle) break;
@@ -532,7 +533,7 @@ __global__ void __launch_bounds__(kTraceBlock) k_extend(SceneView S, const Scene
                 give[rd] = make_int2(lane, *T.bot);
                 __hip_atomic_fetch_add(&parts_of[slot], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
-            __builtin_amdgcn_wave_barrier();
+            wave_sync();
             const bool takes = ((idle >> lane) & 1) && ri < m;
             const int2 gv = takes ? give[ri] : make_int2(lane, 0);
             const int from = gv.x;
@@ -555,7 +556,7 @@ __global__ void __launch_bounds__(kTraceBlock) k_extend(SceneView S, const Scene
                 trace_at(T, gv.y, mine);
                 on = true;
             }
-            __builtin_amdgcn_wave_barrier();
+            wave_sync();
         }
         fetch();
         bool done = step();
