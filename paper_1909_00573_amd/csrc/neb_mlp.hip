@@ -55,10 +55,11 @@ __device__ __forceinline__ f32x4 mfma(bf16x4 a, bf16x4 b, f32x4 c) {
 // a product over two 16-wide k blocks whose A fragments lie side by side:
 // one 16 x 16 x 32 product of gfx950 (kK32; eight k per lane, twice the k in
 // the same issue time; it sums the same terms over a permuted k), or two
-// 16 x 16 x 16 ones.  (A 16 x 16 x 16 product that takes the accumulator of a
-// 16 x 16 x 32 one right behind it, without a wait, which is how the compiler
-// schedules such a pair, gave wrong sums: where the two meet, a wait of the
-// longer one's time stands between them.)
+// 16 x 16 x 16 ones.  (The waits between dependent matrix products of different
+// length are left to software; a 16 x 16 x 16 product that took the accumulator
+// of a 16 x 16 x 32 one right behind it, which is how the compiler schedules
+// such a pair, gave wrong sums.  Where the two meet, wait_products stands
+// between them.)
 template <bool kK32>
 __device__ __forceinline__ f32x4 mfma_pair(bf16x8b a, bf16x4 b0, bf16x4 b1, f32x4 c) {
     if (kK32) {
@@ -68,6 +69,14 @@ __device__ __forceinline__ f32x4 mfma_pair(bf16x8b a, bf16x4 b0, bf16x4 b1, f32x
     }
     c = mfma(bf16x4{a[0], a[1], a[2], a[3]}, b0, c);
     return mfma(bf16x4{a[4], a[5], a[6], a[7]}, b1, c);
+}
+
+// The products that made these accumulators are over once this is: 32 wait
+// states, more than the 19 that the longest product asks for.  The accumulators
+// pass through it, so neither what made them nor what takes them can move
+// across (tests/test_mlp_products_host.py reads the distance off the assembly).
+__device__ __forceinline__ void wait_products(f32x4 (&acc)[4]) {
+    asm volatile("s_nop 15\n\ts_nop 15" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]));
 }
 
 // The encoded input of one sample as the B operand of layer 1: lane group g
@@ -234,13 +243,9 @@ __device__ __forceinline__ void tile_forward(const uint16_t* lds, const float* _
     f32x4 acc[4];
 #pragma unroll
     for (int ob = 0; ob < 4; ++ob) acc[ob] = product64<kK32>(lds, kFragF1, ob * 3, lane, T.x);
-    // the last 16 inputs, after all four blocks of the others and a wait of
-    // 32 cycles (see mfma_pair)
-    if (kK32) {
-        __builtin_amdgcn_sched_barrier(0);
-        asm volatile("s_nop 15\n\ts_nop 15");
-        __builtin_amdgcn_sched_barrier(0);
-    }
+    // the last 16 inputs: a 16 x 16 x 16 product (a 16 x 16 x 32 one with zeros
+    // takes as long and rounds differently)
+    if (kK32) wait_products(acc);
 #pragma unroll
     for (int ob = 0; ob < 4; ++ob) {
         const bf16x8b w = frag(lds, kFragF1, ob * 3 + 2, lane);
