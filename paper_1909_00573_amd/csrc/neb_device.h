@@ -304,12 +304,11 @@ __device__ __forceinline__ bool oct_cell(const OctParams& P, int depth, f3 p, Oc
     return true;
 }
 
-// the node word below inner node word w (< 0) on the way to cell k, `shift`
-// = depth - (level of the child)
-__device__ __forceinline__ int32_t oct_child(const int32_t* __restrict__ nodes, int32_t w, const OctCell& k,
-                                             int shift) {
+// the child of inner node word w (< 0) on the way to cell k, `shift` = depth -
+// (level of the child)
+__device__ __forceinline__ int32_t oct_child(int32_t w, const OctCell& k, int shift) {
     const int32_t child = ((k.c[0] >> shift) & 1) | (((k.c[1] >> shift) & 1) << 1) | (((k.c[2] >> shift) & 1) << 2);
-    return nodes[child - w];
+    return child - w;
 }
 
 // Floor under the area of the surface inside a leaf of diagonal `diag`, so
@@ -320,15 +319,23 @@ __device__ __forceinline__ float oct_area_floor(float diag, bool centre) {
     return diag * diag * (centre ? 0.1f : 0.01f);
 }
 
-// eq. (octdensity) at the leaf (word w, level `level`) holding cell k of the
+// the fresh words, where queries have to add them to the node words
+__device__ __forceinline__ const int32_t* oct_unfolded(const OctState& st, const int32_t* fresh) {
+    return st.folded ? nullptr : fresh;
+}
+// a leaf's count, its word and node given
+__device__ __forceinline__ int32_t oct_count(int32_t w, int32_t at, const int32_t* __restrict__ unfolded) {
+    return (w & kOctCountMask) + (unfolded ? unfolded[at] : 0);
+}
+
+// eq. (octdensity) at the leaf (its count, level `level`) holding cell k of the
 // point p with normal n: the leaf's count over the area of the plane through
 // p inside the leaf's box (eq. area), times the density scale.  centre: the
 // probe at the query point; then *diag_out receives the leaf's diagonal (if
 // the leaf has a count).
 __device__ __forceinline__ float oct_leaf_density(const OctParams& P, float density_scale, int depth,
-                                                  const OctCell& k, int level, int32_t w, f3 p, f3 n, bool centre,
+                                                  const OctCell& k, int level, int32_t count, f3 p, f3 n, bool centre,
                                                   float* diag_out) {
-    const int32_t count = w & kOctCountMask;
     if (count <= 0) return 0.f;
     const int32_t cells = 1 << level;  // per axis at this level
     const int shift = depth - level;
@@ -359,31 +366,34 @@ __device__ __forceinline__ float upper_median(float* v, int n) {
 }
 
 // eq. (octdensity) at the leaf holding p (Appendix B get_density)
-__device__ __forceinline__ float oct_query(const int32_t* __restrict__ nodes, const OctParams& P, float density_scale,
+__device__ __forceinline__ float oct_query(const int32_t* __restrict__ nodes, const int32_t* __restrict__ unfolded,
+                                           const OctParams& P, float density_scale,
                                            int depth, f3 p, f3 n, bool centre, float* diag_out) {
     OctCell k;
     if (!oct_cell(P, depth, p, k)) return 0.f;
-    int32_t w = nodes[P.root];
+    int32_t at = P.root, w = nodes[at];
     int level = 0;
     while (w < 0) {
         ++level;
-        w = oct_child(nodes, w, k, depth - level);
+        at = oct_child(w, k, depth - level);
+        w = nodes[at];
     }
-    return oct_leaf_density(P, density_scale, depth, k, level, w, p, n, centre, diag_out);
+    return oct_leaf_density(P, density_scale, depth, k, level, oct_count(w, at, unfolded), p, n, centre, diag_out);
 }
 
 // Appendix B get_density_robust: the densities at p and at four points
 // offset along the tangents by 1.1 leaf diagonals of p's leaf (1.1e-3
 // scene units when that leaf is empty); the upper median of the non-zero
 // ones (0 if none)
-__device__ __forceinline__ float oct_query_robust(const int32_t* __restrict__ nodes, const OctParams& P,
+__device__ __forceinline__ float oct_query_robust(const int32_t* __restrict__ nodes,
+                                                  const int32_t* __restrict__ unfolded, const OctParams& P,
                                                   float density_scale, int depth, f3 p, f3 n) {
     f3 tx, ty;
     basis(n, tx, ty);
     float diag = 1e-3f;
     float found[5];
     int nf = 0;
-    const float centre = oct_query(nodes, P, density_scale, depth, p, n, true, &diag);
+    const float centre = oct_query(nodes, unfolded, P, density_scale, depth, p, n, true, &diag);
     if (centre > 0.f) found[nf++] = centre;
     const float step = diag * 1.1f;
     const f3 probe[4] = {p + tx * step, p - tx * step, p + ty * step, p - ty * step};
@@ -391,7 +401,7 @@ __device__ __forceinline__ float oct_query_robust(const int32_t* __restrict__ no
     // their node loads are in flight at once (a probe outside the octree's
     // box stops at once with density 0)
     OctCell k[4];
-    int32_t w[4];
+    int32_t w[4], at[4];
     int level[4];
     const int32_t root = nodes[P.root];
 #pragma unroll
@@ -399,6 +409,7 @@ __device__ __forceinline__ float oct_query_robust(const int32_t* __restrict__ no
         const bool in = oct_cell(P, depth, probe[i], k[i]);
         if (!in) k[i].c[0] = k[i].c[1] = k[i].c[2] = 0;
         w[i] = in ? root : 0;
+        at[i] = in ? P.root : -1;
         level[i] = 0;
     }
     while (w[0] < 0 || w[1] < 0 || w[2] < 0 || w[3] < 0) {
@@ -406,9 +417,12 @@ __device__ __forceinline__ float oct_query_robust(const int32_t* __restrict__ no
         for (int i = 0; i < 4; ++i)
             if (w[i] < 0) {
                 ++level[i];
-                w[i] = oct_child(nodes, w[i], k[i], depth - level[i]);
+                at[i] = oct_child(w[i], k[i], depth - level[i]);
+                w[i] = nodes[at[i]];
             }
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = at[i] < 0 ? 0 : oct_count(w[i], at[i], unfolded);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const float r = oct_leaf_density(P, density_scale, depth, k[i], level[i], w[i], probe[i], n, false, nullptr);

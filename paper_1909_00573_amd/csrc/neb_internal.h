@@ -54,6 +54,7 @@ struct OctState {
     alignas(128) int32_t depth;
     int32_t overflow;
     int32_t rejected;
+    int32_t folded;  // 0: deposits of earlier calls are still in the fresh words
     unsigned long long block_iter_sum;
     unsigned long long lost;
     TallyLine deposits[kDepositStripes];
@@ -67,7 +68,7 @@ __host__ __device__ inline unsigned long long oct_deposits(const OctState& st) {
 // a standalone octree (the Appendix-B surface of the C ABI)
 struct Octree {
     int32_t* nodes = nullptr;   // device, capacity words
-    int32_t* fresh = nullptr;   // device, capacity words: deposits of the call in progress, 0 between calls
+    int32_t* fresh = nullptr;   // device, capacity words: deposits that have not joined the node words
     OctState* state = nullptr;  // device
     OctDyn* dyn = nullptr;      // device
     OctParams* prm_dev = nullptr;  // device copy of prm (the kernels take an array of them)
@@ -152,24 +153,26 @@ struct Counters {
 void octree_params_init(OctParams& p, const float smin[3], const float smax[3], int32_t root, int32_t capacity);
 void octree_dyn_for(OctDyn& d, int32_t iter);
 int32_t octree_capacity_rounded(int32_t capacity);
-hipError_t octree_reserve(Octree& o, int64_t n, hipStream_t s);
+hipError_t octree_reserve(Octree& o, int64_t n);
 void octree_release(Octree& o);
 hipError_t octree_reset(Octree& o, hipStream_t s);
 hipError_t octree_increment_xyz(Octree& o, const float* pos, int32_t n, int single, hipStream_t s);
 hipError_t octree_density_xyz(const Octree& o, const float* pos, const float* nrm, int32_t n, int robust, float* out,
                               hipStream_t s);
-hipError_t octree_density_raw(const int32_t* nodes, const OctState* st, const OctParams& P, const OctDyn* dyn,
-                              const float* pos, const float* nrm, int32_t n, int robust, float* out, hipStream_t s);
+hipError_t octree_density_raw(const int32_t* nodes, const int32_t* fresh, const OctState* st, const OctParams& P,
+                              const OctDyn* dyn, const float* pos, const float* nrm, int32_t n, int robust, float* out,
+                              hipStream_t s);
 hipError_t octree_clear(const Octree& o, hipStream_t s);
 // deposits of NEE vertices of many scenes: per-vertex scene from the record
 hipError_t octree_insert_rounds(int32_t* nodes, int32_t* fresh, OctState* states, const OctParams* prm, int n_trees,
-                                const OctDyn* dyn, const float* pos, int stride, const int32_t* scene_of_item, int scene_shift,
-                                const int32_t* n_dev, int32_t n_host, int32_t* const defer[2], int32_t* defer_cnt,
-                                hipStream_t s);
-hipError_t octree_insert_single(int32_t* nodes, OctState* states, const OctParams* prm, const OctDyn* dyn,
-                                const float* pos, int stride, const int32_t* scene_of_item, int scene_shift,
-                                const int32_t* order, int32_t n, hipStream_t s);
-hipError_t octree_init_range(int32_t* nodes, OctState* st, int32_t root, int32_t capacity, hipStream_t s);
+                                const OctDyn* dyn, const float* pos, int stride, const int32_t* scene_of_item,
+                                int scene_shift, const int32_t* n_dev, int32_t n_host,
+                                int32_t* const defer[2], int32_t* defer_cnt, hipStream_t s);
+hipError_t octree_insert_single(int32_t* nodes, const int32_t* fresh, OctState* states, const OctParams* prm,
+                                const OctDyn* dyn, const float* pos, int stride, const int32_t* scene_of_item,
+                                int scene_shift, const int32_t* order, int32_t n, hipStream_t s);
+hipError_t octree_init_range(int32_t* nodes, int32_t* fresh, OctState* st, int32_t root, int32_t capacity,
+                             hipStream_t s);
 hipError_t octree_set_dyn(OctDyn* dyn, const OctDyn& d, hipStream_t s);
 
 }  // namespace neb

@@ -12,9 +12,10 @@
 //  - the listing counts in the node word with compare-and-swap.  Lanes at
 //    one leaf then succeed one per round trip to memory: a leaf that takes
 //    a thousand deposits holds the launch up for milliseconds.  Here the
-//    deposits of a call are added to a second word per node (`fresh`, zero
-//    between calls) with fetch-add, which needs no earlier value, and join
-//    the node words when the call ends (k_oct_fold).  While a call runs, a
+//    deposits of a call are added to a second word per node (`fresh`) with
+//    fetch-add, which needs no earlier value, and join the node words when
+//    the call ends (k_oct_fold), or a later call does (oct_folds): a leaf's
+//    count is the sum of the two.  While a call runs, a
 //    node word only ever changes from the count it began with to a pointer
 //    or to a failed leaf, so any cached copy of a count is the right one.
 //    The deposits whose fetch-add returned less than the leaf's free room
@@ -116,7 +117,8 @@ __device__ __forceinline__ void flush_tally(OctState* st, const SplitTally& T) {
 }
 
 // one deposit by one thread alone (sequential insertion, the oracle's order)
-__device__ __forceinline__ int oct_insert(int32_t* nodes, OctState* st, const OctParams& P, const OctDyn& D, f3 p) {
+__device__ __forceinline__ int oct_insert(int32_t* nodes, const int32_t* fresh, OctState* st, const OctParams& P,
+                                          const OctDyn& D, f3 p) {
     float q[3];
     if (!oct_norm(P, p, q)) return kInsRejected;
     int32_t idx = P.root;
@@ -129,7 +131,7 @@ __device__ __forceinline__ int oct_insert(int32_t* nodes, OctState* st, const Oc
             v = ld_node(nodes + idx);
             continue;
         }
-        int32_t cnt = v & kOctCountMask;
+        const int32_t cnt = oct_count(v, idx, oct_unfolded(*st, fresh));
         bool can_split = !(v & kOctFailed) && level < kOctMaxDepth;
         if (can_split && cnt >= D.split_count) return kInsDeferred;
         int32_t expected = v;
@@ -214,7 +216,7 @@ __device__ __forceinline__ int oct_insert_wave(int32_t* nodes, int32_t* fresh, O
         const int k = grouped ? G.size[my_leader] : 0;
         const int32_t count = v & kOctCountMask;
         const bool bounded = !(v & kOctFailed) && level < kOctMaxDepth;
-        const int limit = bounded ? D.split_count - count : INT32_MAX;  // deposits the leaf takes in this call
+        const int limit = bounded ? D.split_count - count : INT32_MAX;  // what its fresh word can come to
         int l_room = 0;  // of the group's deposits, those the leaf took
         bool l_split = false;
         if (grouped && my_leader == lane && limit > 0) {
@@ -390,9 +392,10 @@ __global__ void __launch_bounds__(256) k_oct_insert_tail(int32_t* nodes, int32_t
 
 // sequential insertion by one thread; order == nullptr means 0..n-1, else
 // the listed items (negative entries skipped)
-__global__ void k_oct_insert_single(int32_t* nodes, OctState* states, const OctParams* prm, const OctDyn* dyn,
-                                    const float* __restrict__ pos, int stride, const int32_t* __restrict__ scene_word,
-                                    int shift, const int32_t* __restrict__ order, int32_t n) {
+__global__ void k_oct_insert_single(int32_t* nodes, const int32_t* fresh, OctState* states, const OctParams* prm,
+                                    const OctDyn* dyn, const float* __restrict__ pos, int stride,
+                                    const int32_t* __restrict__ scene_word, int shift,
+                                    const int32_t* __restrict__ order, int32_t n) {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
     const OctDyn D = *dyn;
     if (D.stop_filling) return;
@@ -401,34 +404,41 @@ __global__ void k_oct_insert_single(int32_t* nodes, OctState* states, const OctP
         if (item < 0) continue;
         const float* pp = pos + (size_t)stride * item;
         int s = item_scene(scene_word, stride, shift, item);
-        int r = oct_insert(nodes, states + s, prm[s], D, mk3(pp[0], pp[1], pp[2]));
+        int r = oct_insert(nodes, fresh, states + s, prm[s], D, mk3(pp[0], pp[1], pp[2]));
         if (r == kInsCounted) states[s].deposits[0].v += 1;
         if (r == kInsRejected) states[s].rejected += 1;
         if (r == kInsDeferred) states[s].lost += 1;  // impossible without concurrency
     }
 }
 
-__global__ void __launch_bounds__(256) k_oct_density_xyz(const int32_t* __restrict__ nodes, const OctState* st,
+__global__ void __launch_bounds__(256) k_oct_density_xyz(const int32_t* __restrict__ nodes,
+                                                         const int32_t* __restrict__ fresh, const OctState* st,
                                                          OctParams P, const OctDyn* dyn, const float* __restrict__ pos,
                                                          const float* __restrict__ nrm, int32_t n, int robust,
                                                          float* __restrict__ out) {
     int depth = st->depth;
     float scale = dyn->density_scale;
+    const int32_t* unfolded = oct_unfolded(*st, fresh);
     for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         f3 p = load3(pos + 3 * (size_t)i);
         f3 nn = normalize3(load3(nrm + 3 * (size_t)i));
-        out[i] = robust ? oct_query_robust(nodes, P, scale, depth, p, nn)
-                        : oct_query(nodes, P, scale, depth, p, nn, false, nullptr);
+        out[i] = robust ? oct_query_robust(nodes, unfolded, P, scale, depth, p, nn)
+                        : oct_query(nodes, unfolded, P, scale, depth, p, nn, false, nullptr);
     }
 }
 
-__global__ void k_oct_init(int32_t* nodes, OctState* st, OctDyn* dyn, int32_t root, int32_t capacity, OctDyn d0) {
-    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < capacity; i += gridDim.x * blockDim.x)
+// fresh: null where its words are zero
+__global__ void k_oct_init(int32_t* nodes, int32_t* fresh, OctState* st, OctDyn* dyn, int32_t root, int32_t capacity,
+                           OctDyn d0) {
+    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < capacity; i += gridDim.x * blockDim.x) {
         nodes[root + i] = 0;
+        if (fresh) fresh[root + i] = 0;
+    }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         st->alloc = root + 1;
         st->depth = 0;
         st->overflow = 0;
+        st->folded = 1;
         st->rejected = 0;
         st->block_iter_sum = 0;
         for (int k = 0; k < kDepositStripes; ++k) st->deposits[k].v = 0;
@@ -437,25 +447,44 @@ __global__ void k_oct_init(int32_t* nodes, OctState* st, OctDyn* dyn, int32_t ro
     }
 }
 
-__global__ void k_oct_clear(int32_t* nodes, OctState* st, int32_t root, int32_t end) {
+__global__ void k_oct_clear(int32_t* nodes, int32_t* fresh, OctState* st, int32_t root, int32_t end) {
     int32_t n = min(st->alloc, end);
+    const bool folded = st->folded != 0;  // fresh words are zero already
     for (int32_t i = root + blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         int32_t v = nodes[i];
         if (v > 0) nodes[i] = 0;
+        if (!folded && fresh[i] != 0) fresh[i] = 0;
     }
     // the ledger restarts
     if (blockIdx.x == 0 && threadIdx.x < kDepositStripes) st->deposits[threadIdx.x].v = 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) st->block_iter_sum = 0;
 }
 
-// The deposits of the call join their leaves' counts; those left at nodes
-// that have split since are part of the split.  Counters and queue lengths
-// return to zero for the next call.  One row of blocks per octree.
-__global__ void __launch_bounds__(256) k_oct_fold(int32_t* nodes, int32_t* fresh, const OctState* states,
-                                                  const OctParams* prm, const OctDyn* dyn, int32_t* cnt) {
+// Whether a call of n deposits per tree has them join the node words.  The
+// sweep reads the fresh word of every allocated node (2^23 nodes 15 us, 2^26
+// 165 us), so on large trees small calls would pay for the tree; without it
+// densities read a second word at each of their leaves.  Deposits and as many
+// robust densities, us, with the sweep and without: 100 points and 2^23 nodes
+// 43 and 31, 2^26 nodes 193 and 32; 100 000 points and 2^23 nodes 76 and 52, 2^26
+// nodes 298 and 61; a million and 2^23 nodes 245 and 285, 2^26 nodes 629 and
+// 384.  Up to 2^20 nodes the sweep is as short as a launch.
+constexpr int32_t kOctFoldNodes = (1 << 20) + 1;
+__device__ __forceinline__ bool oct_folds(int64_t allocated, int64_t n) {
+    return allocated <= kOctFoldNodes || allocated <= 16 * n;
+}
+
+// The deposits join their leaves' counts; those left at nodes that have split
+// since are part of the split.  Counters and queue lengths return to zero for
+// the next call.  One row of blocks per octree.
+__global__ void __launch_bounds__(256) k_oct_fold(int32_t* nodes, int32_t* fresh, OctState* states,
+                                                  const OctParams* prm, const OctDyn* dyn, int32_t* cnt,
+                                                  const int32_t* n_dev, int32_t n_host) {
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) cnt[1] = 0;
     if (dyn->stop_filling) return;
     const int32_t root = prm[blockIdx.y].root, n = min(states[blockIdx.y].alloc, prm[blockIdx.y].end) - root;
+    const bool folds = oct_folds(n, (n_dev ? min(*n_dev, n_host) : n_host) / (int)gridDim.y);
+    if (blockIdx.x == 0 && threadIdx.x == 0) states[blockIdx.y].folded = folds;
+    if (!folds) return;
     for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         const int32_t d = fresh[root + i];
         if (d == 0) continue;
@@ -519,23 +548,25 @@ hipError_t octree_insert_rounds(int32_t* nodes, int32_t* fresh, OctState* states
     }
     hipLaunchKernelGGL(k_oct_insert_tail, dim3(1), dim3(256), 0, s, nodes, fresh, states, prm, dyn, pos, stride,
                        scene_word, shift, defer[0], defer[1], cnt, n_host);
-    hipLaunchKernelGGL(k_oct_fold, dim3(512, n_trees), dim3(256), 0, s, nodes, fresh, states, prm, dyn, cnt);
+    hipLaunchKernelGGL(k_oct_fold, dim3(512, n_trees), dim3(256), 0, s, nodes, fresh, states, prm, dyn, cnt, n_dev,
+                       n_host);
     return hipGetLastError();
 }
 
-hipError_t octree_insert_single(int32_t* nodes, OctState* states, const OctParams* prm, const OctDyn* dyn,
-                                const float* pos, int stride, const int32_t* scene_word, int shift,
+hipError_t octree_insert_single(int32_t* nodes, const int32_t* fresh, OctState* states, const OctParams* prm,
+                                const OctDyn* dyn, const float* pos, int stride, const int32_t* scene_word, int shift,
                                 const int32_t* order, int32_t n, hipStream_t s) {
-    hipLaunchKernelGGL(k_oct_insert_single, dim3(1), dim3(64), 0, s, nodes, states, prm, dyn, pos, stride, scene_word,
-                       shift, order, n);
+    hipLaunchKernelGGL(k_oct_insert_single, dim3(1), dim3(64), 0, s, nodes, fresh, states, prm, dyn, pos, stride,
+                       scene_word, shift, order, n);
     return hipGetLastError();
 }
 
-hipError_t octree_init_range(int32_t* nodes, OctState* st, int32_t root, int32_t capacity, hipStream_t s) {
+hipError_t octree_init_range(int32_t* nodes, int32_t* fresh, OctState* st, int32_t root, int32_t capacity,
+                             hipStream_t s) {
     OctDyn d0;
     octree_dyn_for(d0, 1);
-    hipLaunchKernelGGL(k_oct_init, dim3(grid_for(capacity, 256)), dim3(256), 0, s, nodes, st, (OctDyn*)nullptr, root,
-                       capacity, d0);
+    hipLaunchKernelGGL(k_oct_init, dim3(grid_for(capacity, 256)), dim3(256), 0, s, nodes,
+                       capacity > kOctFoldNodes ? fresh : nullptr, st, (OctDyn*)nullptr, root, capacity, d0);
     return hipGetLastError();
 }
 
@@ -547,19 +578,9 @@ hipError_t octree_set_dyn(OctDyn* dyn, const OctDyn& d, hipStream_t s) {
 // ---------------------------------------------------------------------------
 // standalone octree: one octree, root 0, params copied to the device
 // ---------------------------------------------------------------------------
-hipError_t octree_reserve(Octree& o, int64_t n, hipStream_t s) {
+hipError_t octree_reserve(Octree& o, int64_t n) {
     hipError_t e = hipSuccess;
-    if (!o.defer_cnt) {
-        e = hipMalloc(&o.defer_cnt, 4 * 3);
-        if (e == hipSuccess) hipLaunchKernelGGL(k_oct_zero, dim3(1), dim3(64), 0, s, o.defer_cnt, (int64_t)3);
-    }
-    if (!o.fresh && e == hipSuccess) {
-        e = hipMalloc(&o.fresh, 4 * (size_t)o.capacity);
-        if (e == hipSuccess)
-            hipLaunchKernelGGL(k_oct_zero, dim3(grid_for(o.capacity, 256)), dim3(256), 0, s, o.fresh,
-                               (int64_t)o.capacity);
-    }
-    if (e != hipSuccess || n <= o.defer_cap) return e;
+    if (n <= o.defer_cap) return e;
     if (o.defer[0]) (void)hipFree(o.defer[0]);
     if (o.defer[1]) (void)hipFree(o.defer[1]);
     o.defer[0] = o.defer[1] = nullptr;
@@ -585,36 +606,39 @@ void octree_release(Octree& o) {
 hipError_t octree_reset(Octree& o, hipStream_t s) {
     OctDyn d0;
     octree_dyn_for(d0, 1);
-    hipLaunchKernelGGL(k_oct_init, dim3(grid_for(o.capacity, 256)), dim3(256), 0, s, o.nodes, o.state, o.dyn, 0,
-                       o.capacity, d0);
+    hipLaunchKernelGGL(k_oct_init, dim3(grid_for(o.capacity, 256)), dim3(256), 0, s, o.nodes, o.fresh, o.state, o.dyn,
+                       0, o.capacity, d0);
+    hipLaunchKernelGGL(k_oct_zero, dim3(1), dim3(64), 0, s, o.defer_cnt, (int64_t)3);
     return hipGetLastError();
 }
 
 hipError_t octree_increment_xyz(Octree& o, const float* pos, int32_t n, int single, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    if (single) return octree_insert_single(o.nodes, o.state, o.prm_dev, o.dyn, pos, 3, nullptr, 0, nullptr, n, s);
-    hipError_t e = octree_reserve(o, n, s);
+    if (single)
+        return octree_insert_single(o.nodes, o.fresh, o.state, o.prm_dev, o.dyn, pos, 3, nullptr, 0, nullptr, n, s);
+    hipError_t e = octree_reserve(o, n);
     if (e != hipSuccess) return e;
     return octree_insert_rounds(o.nodes, o.fresh, o.state, o.prm_dev, 1, o.dyn, pos, 3, nullptr, 0, nullptr, n,
                                 o.defer, o.defer_cnt, s);
 }
 
-hipError_t octree_density_raw(const int32_t* nodes, const OctState* st, const OctParams& P, const OctDyn* dyn,
-                              const float* pos, const float* nrm, int32_t n, int robust, float* out, hipStream_t s) {
+hipError_t octree_density_raw(const int32_t* nodes, const int32_t* fresh, const OctState* st, const OctParams& P,
+                              const OctDyn* dyn, const float* pos, const float* nrm, int32_t n, int robust, float* out,
+                              hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_oct_density_xyz, dim3(grid_for(n, 256)), dim3(256), 0, s, nodes, st, P, dyn, pos, nrm, n,
-                       robust, out);
+    hipLaunchKernelGGL(k_oct_density_xyz, dim3(grid_for(n, 256)), dim3(256), 0, s, nodes, fresh, st, P, dyn, pos, nrm,
+                       n, robust, out);
     return hipGetLastError();
 }
 
 hipError_t octree_density_xyz(const Octree& o, const float* pos, const float* nrm, int32_t n, int robust, float* out,
                               hipStream_t s) {
-    return octree_density_raw(o.nodes, o.state, o.prm, o.dyn, pos, nrm, n, robust, out, s);
+    return octree_density_raw(o.nodes, o.fresh, o.state, o.prm, o.dyn, pos, nrm, n, robust, out, s);
 }
 
 hipError_t octree_clear(const Octree& o, hipStream_t s) {
-    hipLaunchKernelGGL(k_oct_clear, dim3(grid_for(o.capacity, 256)), dim3(256), 0, s, o.nodes, o.state, o.prm.root,
-                       o.prm.end);
+    hipLaunchKernelGGL(k_oct_clear, dim3(grid_for(o.capacity, 256)), dim3(256), 0, s, o.nodes, o.fresh, o.state,
+                       o.prm.root, o.prm.end);
     return hipGetLastError();
 }
 

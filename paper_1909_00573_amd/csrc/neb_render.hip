@@ -845,7 +845,8 @@ __device__ __forceinline__ float set_density(const DGrid& D, int s, f3 x, float 
 // density of NEE vertices at x (geometric normal nn) in scene s, from the
 // octree, the density grid or the analytic test density
 __device__ __forceinline__ float point_density(const RenderArgs& A, int s, f3 x, f3 nn, const int32_t* __restrict__ nodes,
-                                               const OctState* ost, const OctParams* prm, float scale) {
+                                               const int32_t* __restrict__ fresh, const OctState* ost,
+                                               const OctParams* prm, float scale) {
     if (A.density_mode == NEB_DENSITY_ANALYTIC) {
         const SceneInfo& I = A.sc[s];
         return I.rho0 + I.cam_w * cam_hit_density(I.cam, x, nn);
@@ -854,8 +855,10 @@ __device__ __forceinline__ float point_density(const RenderArgs& A, int s, f3 x,
         const SceneInfo& I = A.sc[s];
         return set_density<kKnnMax, 1>(A.dg, s, x, I.dr, I.inv_dcell, A.density_mode, I.knn_k, 0);
     }
-    if (A.density_mode == NEB_DENSITY_OCTREE) return oct_query(nodes, prm[s], scale, ost[s].depth, x, nn, false, nullptr);
-    return oct_query_robust(nodes, prm[s], scale, ost[s].depth, x, nn);
+    const int32_t* unfolded = oct_unfolded(ost[s], fresh);
+    if (A.density_mode == NEB_DENSITY_OCTREE)
+        return oct_query(nodes, unfolded, prm[s], scale, ost[s].depth, x, nn, false, nullptr);
+    return oct_query_robust(nodes, unfolded, prm[s], scale, ost[s].depth, x, nn);
 }
 
 // density grid over this iteration's NEE vertices, built as the merge grid is:
@@ -952,13 +955,14 @@ __global__ void __launch_bounds__(256) k_pset_query(const float* q, int32_t n, D
 }
 
 __global__ void __launch_bounds__(256) k_density(RenderArgs A, VertexStore V, const int32_t* n_vertices,
-                                                 const int32_t* __restrict__ nodes, const OctState* ost,
+                                                 const int32_t* __restrict__ nodes,
+                                                 const int32_t* __restrict__ fresh, const OctState* ost,
                                                  const OctParams* prm, const OctDyn* dyn) {
     int n = *n_vertices;
     const float scale = dyn->density_scale;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         float4 a1 = V.v1[i];
-        V.rho[i] = point_density(A, tag_scene(fbits(a1.w)), xyz(V.v0[i]), xyz(a1), nodes, ost, prm, scale);
+        V.rho[i] = point_density(A, tag_scene(fbits(a1.w)), xyz(V.v0[i]), xyz(a1), nodes, fresh, ost, prm, scale);
     }
 }
 
@@ -1282,7 +1286,8 @@ __global__ void __launch_bounds__(256) k_lp_emit(RenderArgs A, PhotonQ pq, int32
 // and U for k_photon.  A photon whose emission density vanishes (grazing
 // hit) carries no weight and is dropped.
 __global__ void __launch_bounds__(256) k_lp_first(RenderArgs A, PhotonQ pq, int2* hits,
-                                                  const int32_t* __restrict__ nodes, const OctState* ost,
+                                                  const int32_t* __restrict__ nodes,
+                                                 const int32_t* __restrict__ fresh, const OctState* ost,
                                                   const OctParams* prm, const OctDyn* dyn) {
     const int n = A.cnt->lp_count;
     const SceneView& S = A.S;
@@ -1306,7 +1311,7 @@ __global__ void __launch_bounds__(256) k_lp_first(RenderArgs A, PhotonQ pq, int2
         float cos_y = fabsf(dot3(ny, w));
         float p_light = area ? l0.w / l1.w : l0.w;
         float rl = emission_density(area, dot3(ln, w), cos_y, d2);
-        float rho = A.photons ? point_density(A, sid, y, ny, nodes, ost, prm, scale) : 0.f;
+        float rho = A.photons ? point_density(A, sid, y, ny, nodes, fresh, ost, prm, scale) : 0.f;
         float c1 = 1.0f + rho / (I.nlp * rl);
         float e = (1.0f + 1.0f / (I.nlp * I.r2pi * rl)) / c1;
         float X = area ? 1.0f / (cos_y * p_light * I.nlp * I.r * I.r * c1) : 0.f;
@@ -2021,13 +2026,15 @@ __global__ void __launch_bounds__(256) k_mlp_collect(VertexStore V, const int32_
 // the expected number of probes is n_probe and the choice does not depend on
 // the order of the vertex store.
 __global__ void __launch_bounds__(256) k_mlp_probe(VertexStore V, const int32_t* n_vertices,
-                                                   const int32_t* __restrict__ nodes, const OctState* ost,
+                                                   const int32_t* __restrict__ nodes,
+                                                 const int32_t* __restrict__ fresh, const OctState* ost,
                                                    OctParams P, const OctDyn* dyn, int all, int n_probe, uint32_t k0,
                                                    uint32_t k1, const Counters* cnt, int32_t* total, int32_t* bad,
                                                    float* sums, float max_rel, unsigned long long* mc) {
     const int nv = *n_vertices;
     const int depth = ost->depth;
     const float scale = dyn->density_scale;
+    const int32_t* unfolded = oct_unfolded(*ost, fresh);
     const uint32_t it = (uint32_t)cnt->iter;
     const uint64_t lim = (uint64_t)n_probe << 24;
     unsigned probes = 0, nbad = 0;
@@ -2040,7 +2047,7 @@ __global__ void __launch_bounds__(256) k_mlp_probe(VertexStore V, const int32_t*
         }
         f3 x = xyz(a0), nn = xyz(a1);
         float rm = V.rho[i];
-        float ro = oct_query_robust(nodes, P, scale, depth, x, nn);
+        float ro = oct_query_robust(nodes, unfolded, P, scale, depth, x, nn);
         bool b = ro > 0.f ? fabsf(rm - ro) > max_rel * ro : rm > 0.f;
         int r = region_of(P, x);
         atomicAdd(total + r, 1);
@@ -2094,16 +2101,18 @@ __global__ void k_mlp_clear_gate_counts(unsigned long long* mc) {
 // vertices in disabled regions take the robust octree query instead
 __global__ void __launch_bounds__(256) k_density_fallback(VertexStore V, const int32_t* n_vertices,
                                                           const int32_t* __restrict__ gate,
-                                                          const int32_t* __restrict__ nodes, const OctState* ost,
+                                                          const int32_t* __restrict__ nodes,
+                                                 const int32_t* __restrict__ fresh, const OctState* ost,
                                                           OctParams P, const OctDyn* dyn, unsigned long long* mc) {
     const int n = *n_vertices;
     const int depth = ost->depth;
     const float scale = dyn->density_scale;
+    const int32_t* unfolded = oct_unfolded(*ost, fresh);
     unsigned fb = 0;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         f3 x = xyz(V.v0[i]);
         if (gate[region_of(P, x)]) continue;
-        V.rho[i] = oct_query_robust(nodes, P, scale, depth, x, xyz(V.v1[i]));
+        V.rho[i] = oct_query_robust(nodes, unfolded, P, scale, depth, x, xyz(V.v1[i]));
         ++fb;
     }
     wave_add_u64(mc + kMlpCntFallback, fb);
@@ -2189,7 +2198,7 @@ struct neb_ctx_s {
     std::vector<void*> scene_allocs;
     // octree pool: scene s owns [oct_prm[s].root, oct_prm[s].end)
     int32_t* oct_nodes = nullptr;
-    int32_t* oct_fresh = nullptr;  // deposits of the iteration in progress, 0 between iterations
+    int32_t* oct_fresh = nullptr;  // deposits that have not joined the node words
     OctState* oct_states = nullptr;
     OctParams* oct_prm_dev = nullptr;
     OctDyn* oct_dyn = nullptr;
@@ -2871,7 +2880,7 @@ static neb_status restart(neb_ctx c, hipStream_t s) {
                        12 * (int64_t)c->npix);
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, (int32_t*)c->cnt, 0, (int64_t)(sizeof(Counters) / 4));
     for (int i = 0; i < c->n_scenes; ++i)
-        HIP_TRY(octree_init_range(c->oct_nodes, c->oct_states + i, c->oct_prm[i].root,
+        HIP_TRY(octree_init_range(c->oct_nodes, c->oct_fresh, c->oct_states + i, c->oct_prm[i].root,
                                   c->oct_prm[i].end - c->oct_prm[i].root, s));
     OctDyn d0;
     octree_dyn_for(d0, 1);
@@ -3274,8 +3283,8 @@ static neb_status enqueue_iteration(neb_ctx c, hipStream_t s, int parity, bool c
         const int32_t* tagw = (const int32_t*)c->V.v1 + 3;
         prof_begin(c, K_OCTREE_INSERT, s);
         if (c->slots)
-            e = octree_insert_single(c->oct_nodes, c->oct_states, c->oct_prm_dev, c->oct_dyn, pos, 4, tagw, 8, c->slots,
-                                     (int32_t)c->slot_cap, s);
+            e = octree_insert_single(c->oct_nodes, c->oct_fresh, c->oct_states, c->oct_prm_dev, c->oct_dyn, pos, 4,
+                                     tagw, 8, c->slots, (int32_t)c->slot_cap, s);
         else
             e = octree_insert_rounds(c->oct_nodes, c->oct_fresh, c->oct_states, c->oct_prm_dev, c->n_scenes, c->oct_dyn,
                                      pos, 4, tagw, 8,
@@ -3294,7 +3303,8 @@ static neb_status enqueue_iteration(neb_ctx c, hipStream_t s, int parity, bool c
         if (j == 1 || (j - 1) % c->mcfg.probe_every == 0) {
             hipLaunchKernelGGL(k_mlp_probe, dim3(grid_of(vcap, 256, 4096)), dim3(256), 0, s, c->V,
                                (const int32_t*)nv, (const int32_t*)c->oct_nodes,
-                               (const OctState*)c->oct_states, P0, (const OctDyn*)c->oct_dyn, j == 1 ? 1 : 0,
+                               (const int32_t*)c->oct_fresh, (const OctState*)c->oct_states, P0,
+                               (const OctDyn*)c->oct_dyn, j == 1 ? 1 : 0,
                                c->mcfg.probes, c->mcfg.seed, 0x50524F42u, (const Counters*)cnt, c->reg_total,
                                c->reg_bad, c->reg_sum, c->mcfg.max_rel_error, c->mlp_cnt);
             hipLaunchKernelGGL(k_mlp_clear_gate_counts, dim3(1), dim3(1), 0, s, c->mlp_cnt);
@@ -3304,7 +3314,8 @@ static neb_status enqueue_iteration(neb_ctx c, hipStream_t s, int parity, bool c
         }
         hipLaunchKernelGGL(k_density_fallback, dim3(grid_of(vcap, 256)), dim3(256), 0, s, c->V,
                            (const int32_t*)nv, (const int32_t*)c->reg_gate,
-                           (const int32_t*)c->oct_nodes, (const OctState*)c->oct_states, P0,
+                           (const int32_t*)c->oct_nodes, (const int32_t*)c->oct_fresh,
+                           (const OctState*)c->oct_states, P0,
                            (const OctDyn*)c->oct_dyn, c->mlp_cnt);
         prof_end(c, s);
     } else if (need_rho && set_mode) {
@@ -3317,7 +3328,8 @@ static neb_status enqueue_iteration(neb_ctx c, hipStream_t s, int parity, bool c
     } else if (need_rho) {
         TIMED(K_DENSITY, hipLaunchKernelGGL(k_density, dim3(grid_of(vcap, 256)), dim3(256), 0, s, A, c->V,
                                             (const int32_t*)nv, (const int32_t*)c->oct_nodes,
-                                            (const OctState*)c->oct_states, (const OctParams*)c->oct_prm_dev,
+                                            (const int32_t*)c->oct_fresh, (const OctState*)c->oct_states,
+                                            (const OctParams*)c->oct_prm_dev,
                                             (const OctDyn*)c->oct_dyn));
     }
     // NEE recycling: the vertices by cells of the recycling radius and n_E
@@ -3360,7 +3372,8 @@ static neb_status enqueue_iteration(neb_ctx c, hipStream_t s, int parity, bool c
             if (j == 1 && lp)
                 TIMED(K_LIGHT_PHOTON,
                       hipLaunchKernelGGL(k_lp_first, dim3(grid_of(c->n_lp, 256)), dim3(256), 0, s, A, c->pq[0], hj,
-                                         (const int32_t*)c->oct_nodes, (const OctState*)c->oct_states,
+                                         (const int32_t*)c->oct_nodes, (const int32_t*)c->oct_fresh,
+                                         (const OctState*)c->oct_states,
                                          (const OctParams*)c->oct_prm_dev, (const OctDyn*)c->oct_dyn));
             if (ordered) {
                 // photons in the spatial order of their hits; the order array
@@ -3775,7 +3788,7 @@ extern "C" neb_status neb_query_density(neb_ctx c, const float* pos, const float
     hipStream_t s = (hipStream_t)stream;
     const OctParams& P = c->oct_prm[0];
     if (is_dev) {
-        HIP_TRY(octree_density_raw(c->oct_nodes, c->oct_states, P, c->oct_dyn, pos, nrm, n, 1, out, s));
+        HIP_TRY(octree_density_raw(c->oct_nodes, c->oct_fresh, c->oct_states, P, c->oct_dyn, pos, nrm, n, 1, out, s));
         return NEB_OK;
     }
     float *dp = nullptr, *dn = nullptr, *dout = nullptr;
@@ -3790,7 +3803,8 @@ extern "C" neb_status neb_query_density(neb_ctx c, const float* pos, const float
     neb_status st = NEB_OK;
     if (hipMemcpy(dp, pos, 12 * (size_t)n, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(dn, nrm, 12 * (size_t)n, hipMemcpyHostToDevice) != hipSuccess ||
-        octree_density_raw(c->oct_nodes, c->oct_states, P, c->oct_dyn, dp, dn, n, 1, dout, s) != hipSuccess ||
+        octree_density_raw(c->oct_nodes, c->oct_fresh, c->oct_states, P, c->oct_dyn, dp, dn, n, 1, dout, s) !=
+            hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess ||
         hipMemcpy(out, dout, 4 * (size_t)n, hipMemcpyDeviceToHost) != hipSuccess)
         st = fail(NEB_ERR_DEVICE, "neb_query_density transfer failed");
@@ -3798,15 +3812,31 @@ extern "C" neb_status neb_query_density(neb_ctx c, const float* pos, const float
     return st;
 }
 
-// info of the octree that owns [root, end) of a pool
-static neb_status octree_info(const int32_t* pool, const OctState* state, int32_t root, int32_t end, hipStream_t s,
-                              int64_t info[8]) {
+// words [root, root + n) of an octree of a pool, to host memory; the first
+// `used` are allocated
+static neb_status octree_words(const int32_t* pool, const int32_t* fresh, int32_t folded, int32_t root, int32_t used,
+                               int32_t n, int32_t* words) {
+    HIP_TRY(hipMemcpy(words, pool + root, 4 * (size_t)n, hipMemcpyDeviceToHost));
+    if (folded) return NEB_OK;
+    std::vector<int32_t> more((size_t)std::min(used, n));
+    HIP_TRY(hipMemcpy(more.data(), fresh + root, 4 * more.size(), hipMemcpyDeviceToHost));
+    for (size_t i = 0; i < more.size(); ++i)
+        if (words[i] >= 0) words[i] += more[i];
+    return NEB_OK;
+}
+
+// info of the octree that owns [root, end) of a pool, and its words (null: none)
+static neb_status octree_info(const int32_t* pool, const int32_t* fresh, const OctState* state, int32_t root,
+                              int32_t end, hipStream_t s, int64_t info[8], int32_t* words = nullptr, int32_t cap = 0) {
     OctState st;
     HIP_TRY(hipStreamSynchronize(s));
     HIP_TRY(hipMemcpy(&st, state, sizeof(st), hipMemcpyDeviceToHost));
     int32_t used = std::min(st.alloc, end) - root;
     std::vector<int32_t> nodes((size_t)std::max(used, 0));
-    if (used > 0) HIP_TRY(hipMemcpy(nodes.data(), pool + root, 4 * (size_t)used, hipMemcpyDeviceToHost));
+    if (used > 0) {
+        neb_status r = octree_words(pool, fresh, st.folded, root, used, used, nodes.data());
+        if (r != NEB_OK) return r;
+    }
     int64_t leaf = 0;
     for (int32_t v : nodes)
         if (v >= 0) leaf += v & kOctCountMask;
@@ -3818,6 +3848,7 @@ static neb_status octree_info(const int32_t* pool, const OctState* state, int32_
     info[5] = st.overflow;
     info[6] = st.rejected;
     info[7] = (int64_t)st.lost;
+    if (words && cap > 0) return octree_words(pool, fresh, st.folded, root, used, std::min(cap, end - root), words);
     return NEB_OK;
 }
 
@@ -3878,8 +3909,8 @@ extern "C" neb_status neb_get_stats(neb_ctx c, neb_stats* out) {
         // octree fields: summed over the scenes of the batch (depth: the deepest)
         for (int s = 0; s < c->n_scenes; ++s) {
             int64_t info[8];
-            neb_status st = octree_info(c->oct_nodes, c->oct_states + s, c->oct_prm[s].root, c->oct_prm[s].end,
-                                        c->last_stream, info);
+            neb_status st = octree_info(c->oct_nodes, c->oct_fresh, c->oct_states + s, c->oct_prm[s].root,
+                                        c->oct_prm[s].end, c->last_stream, info);
             if (st != NEB_OK) return st;
             out->oct_capacity += info[0];
             out->oct_allocated += info[1];
@@ -3909,12 +3940,8 @@ extern "C" neb_status neb_get_scene_octree(neb_ctx c, int32_t scene, int32_t* no
     neb_status st = check_scene_ready(c, scene);
     if (st != NEB_OK) return st;
     const OctParams& P = c->oct_prm[scene];
-    st = octree_info(c->oct_nodes, c->oct_states + scene, P.root, P.end, c->last_stream, info);
-    if (st != NEB_OK) return st;
-    if (nodes && cap > 0)
-        HIP_TRY(hipMemcpy(nodes, c->oct_nodes + P.root, 4 * (size_t)std::min(cap, P.end - P.root),
-                          hipMemcpyDeviceToHost));
-    return NEB_OK;
+    return octree_info(c->oct_nodes, c->oct_fresh, c->oct_states + scene, P.root, P.end, c->last_stream, info, nodes,
+                       cap);
 }
 
 extern "C" neb_status neb_get_octree(neb_ctx c, int32_t* nodes, int32_t cap, int64_t info[8]) {
@@ -4379,6 +4406,8 @@ extern "C" neb_status neb_octree_create(const float scene_min[3], const float sc
     t.capacity = t.prm.end;
     t.last_iter = 1;
     hipError_t e = hipMalloc(&t.nodes, 4 * (size_t)t.capacity);
+    if (e == hipSuccess) e = hipMalloc(&t.fresh, 4 * (size_t)t.capacity);
+    if (e == hipSuccess) e = hipMalloc(&t.defer_cnt, 4 * 3);
     if (e == hipSuccess) e = hipMalloc(&t.state, sizeof(OctState));
     if (e == hipSuccess) e = hipMalloc(&t.dyn, sizeof(OctDyn));
     if (e == hipSuccess) e = hipMalloc(&t.prm_dev, sizeof(OctParams));
@@ -4432,11 +4461,7 @@ extern "C" neb_status neb_octree_clear_counters(neb_octree o, void* stream) {
 
 extern "C" neb_status neb_octree_export(neb_octree o, int32_t* nodes, int32_t cap, int64_t info[8], void* stream) {
     if (!o || !info) return fail(NEB_ERR_INVALID_ARG, "null pointer");
-    neb_status st = octree_info(o->o.nodes, o->o.state, 0, o->o.capacity, (hipStream_t)stream, info);
-    if (st != NEB_OK) return st;
-    if (nodes && cap > 0)
-        HIP_TRY(hipMemcpy(nodes, o->o.nodes, 4 * (size_t)std::min(cap, o->o.capacity), hipMemcpyDeviceToHost));
-    return NEB_OK;
+    return octree_info(o->o.nodes, o->o.fresh, o->o.state, 0, o->o.capacity, (hipStream_t)stream, info, nodes, cap);
 }
 
 extern "C" void neb_octree_destroy(neb_octree o) {
