@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "neb.h"
+#include "neb_trace_shape.h"
 
 namespace neb {
 
@@ -14,7 +15,6 @@ constexpr int32_t kOctFailed = 0x40000000; // "split failed" mark on a full leaf
 constexpr int32_t kOctCountMask = 0x3FFFFFFF;
 constexpr int kMaxPathLen = 16;
 constexpr int kBvhStackMax = 64;           // deepest LDS traversal stack (entries per lane)
-constexpr int kTraceBlock = 64;            // threads per traversal block (one wave)
 
 constexpr uint32_t kTagCamera = 1, kTagBsdf = 2, kTagNee = 3, kTagPhoton = 4, kTagMlp = 5, kTagProbe = 6,
                    kTagLight = 7;

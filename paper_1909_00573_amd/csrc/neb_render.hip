@@ -400,7 +400,6 @@ __device__ __forceinline__ int hit_bin(const HitBins& B, int scene, f3 y) {
 // Alone, per iteration: city camera rays 7.17 -> 2.47 ms, photon rays 5.68 ->
 // 1.90 ms; room (512 x 512) camera rays 0.92 -> 0.60 ms, photon rays 1.45 ->
 // 0.90 ms, against a kernel that tested leaves where it met them.
-constexpr int kDealRays = 16;
 template <int kStack, bool kAnyHit, typename Off, bool kDeal>
 __global__ void __launch_bounds__(kTraceBlock) k_extend(SceneView S, const SceneInfo* sc,
                                                         const float4* __restrict__ org,
@@ -475,7 +474,7 @@ __global__ void __launch_bounds__(kTraceBlock) k_extend(SceneView S, const Scene
     // A queue of at most kDealRays rays per wave of the launch is dealt out at
     // once (kDeal), and the walk starts with the sharing below: a wave of 64 grazing
     // rays has no lane free to help while other SIMDs have no wave at all.
-    // Each XCD takes a contiguous part.  (deals_rays has the figures.)
+    // Each XCD takes a contiguous part.  (trace_deals has the figures.)
     const bool dealt = kDeal && n <= kDealRays * (int)gridDim.x;
     const int per = (n + (int)gridDim.x - 1) / (int)gridDim.x;
     const int w = gridDim.x & 7 ? (int)blockIdx.x
@@ -2392,22 +2391,9 @@ static uint32_t next_pow2(uint64_t v) {
 
 static int lds_blocks_per_cu(int stack) { return (160 * 1024) / (stack * kTraceBlock * 4); }
 
-// blocks of a traversal launch over a queue of at most cap rays, with bpc
-// blocks per CU (0: one block per 64 queue slots, -1: as many as the LDS holds)
-// Closest-hit launches deal short queues out in contexts of at most 65 536
-// pixels, whose queues leave most of the chip without a wave.  City of 120 x 120 lots at 160 x 120, two iterations:
-// 7.2 -> 2.6 ms; of 12 x 12 lots at 60 x 50 1.50 -> 0.66; 64 x 64 preview 1.29
-// -> 1.11.  Larger frames lose by it (waves with few rays beside the other
-// streams' kernels): 401 x 227 room 5.76 -> 5.83 ms, 1024 x 1024 city 12.33 -> 12.46.
-static bool deals_rays(neb_ctx c) { return c->npix <= 65536; }
+static bool deals_rays(neb_ctx c) { return trace_deals(c->npix, c->node_bytes, c->tri_bytes); }
 static int trace_grid(neb_ctx c, int64_t cap, int bpc) {
-    if (bpc < 0 || bpc > lds_blocks_per_cu(c->cfg.stack)) bpc = lds_blocks_per_cu(c->cfg.stack);
-    // never more blocks than the queue has lanes' worth of rays, or than
-    // leave a wave eight rays of it where the queue is dealt out (two: 60 x 50
-    // city 0.82 instead of 0.66 ms)
-    const int least = deals_rays(c) ? 8 : kTraceBlock;
-    if (bpc > 0) return std::max(1, (int)std::min<int64_t>((int64_t)c->cus * bpc, (cap + least - 1) / least));
-    return grid_of(cap, kTraceBlock, 1 << 20);
+    return trace_blocks(c->cus, cap, bpc, lds_blocks_per_cu(c->cfg.stack), deals_rays(c));
 }
 
 static void drop_graph(neb_ctx c) {
@@ -3087,8 +3073,7 @@ static RenderArgs make_args(neb_ctx c) {
     return A;
 }
 
-// 32-bit byte offsets hold for pools of at most 4 GB
-static bool small_pools(neb_ctx c) { return std::max(c->node_bytes, c->tri_bytes) <= (int64_t)UINT32_MAX; }
+static bool small_pools(neb_ctx c) { return trace_small_pools(c->node_bytes, c->tri_bytes); }
 
 template <int kStack, typename Off, bool kDeal>
 static void launch_extend_(neb_ctx c, int64_t cap, const float4* org, const float4* dir, int32_t* count, int32_t* next,
