@@ -412,6 +412,7 @@ __global__ void __launch_bounds__(kTraceBlock) k_extend(SceneView S, const Scene
     __shared__ unsigned long long res[kTraceBlock];  // split rays, by the lane that took the ray: nearest hit so far
     __shared__ int parts_of[kTraceBlock];            // ... and the lanes that still walk it
     __shared__ int2 give[kTraceBlock];               // (donor lane, step) of the r-th donation
+    static_assert(sizeof(stack) + sizeof(res) + sizeof(parts_of) + sizeof(give) == trace_lds_bytes(kStack));
     const int n = *count;
     if (next_count && blockIdx.x == 0 && threadIdx.x == 0) *next_count = 0;
     unsigned traced = 0, nodes = 0, tris = 0;
@@ -2389,11 +2390,9 @@ static uint32_t next_pow2(uint64_t v) {
     return (uint32_t)p;
 }
 
-static int lds_blocks_per_cu(int stack) { return (160 * 1024) / (stack * kTraceBlock * 4); }
-
 static bool deals_rays(neb_ctx c) { return trace_deals(c->npix, c->node_bytes, c->tri_bytes); }
 static int trace_grid(neb_ctx c, int64_t cap, int bpc) {
-    return trace_blocks(c->cus, cap, bpc, lds_blocks_per_cu(c->cfg.stack), deals_rays(c));
+    return trace_blocks(c->cus, cap, bpc, trace_blocks_resident(c->cfg.stack), deals_rays(c));
 }
 
 static void drop_graph(neb_ctx c) {
@@ -3985,9 +3984,9 @@ static neb_status apply_config(neb_ctx c, const neb_launch_config& cfg) {
         return fail(NEB_ERR_INVALID_ARG, "bvh_stack must be 32, 48 or 64");
     if (c->ready && cfg.bvh_stack <= c->forest_depth)
         return fail(NEB_ERR_CAPACITY, "bvh_stack must exceed the stack entries every BVH needs");
-    if (cfg.trace_blocks_per_cu < -1 || cfg.trace_blocks_per_cu > lds_blocks_per_cu(cfg.bvh_stack))
+    if (cfg.trace_blocks_per_cu < -1 || cfg.trace_blocks_per_cu > trace_blocks_accepted(cfg.bvh_stack))
         return fail(NEB_ERR_INVALID_ARG, "trace_blocks_per_cu out of range for this stack");
-    if (cfg.nee_blocks_per_cu < -1 || cfg.nee_blocks_per_cu > lds_blocks_per_cu(cfg.bvh_stack))
+    if (cfg.nee_blocks_per_cu < -1 || cfg.nee_blocks_per_cu > trace_blocks_accepted(cfg.bvh_stack))
         return fail(NEB_ERR_INVALID_ARG, "nee_blocks_per_cu out of range for this stack");
     if (cfg.photon_blocks_per_cu < 0 || cfg.photon_blocks_per_cu > 64)
         return fail(NEB_ERR_INVALID_ARG, "photon_blocks_per_cu out of range (0..64)");
@@ -4011,7 +4010,7 @@ extern "C" neb_status neb_set_launch_config(neb_ctx c, const neb_launch_config* 
 extern "C" neb_status neb_get_launch_config(neb_ctx c, neb_launch_config* cfg) {
     if (!c || !cfg) return fail(NEB_ERR_INVALID_ARG, "null pointer");
     cfg->bvh_stack = c->cfg.stack;
-    const int maxb = lds_blocks_per_cu(c->cfg.stack);
+    const int maxb = trace_blocks_resident(c->cfg.stack);
     cfg->trace_blocks_per_cu = c->cfg.trace_bpc < 0 ? maxb : std::min(c->cfg.trace_bpc, maxb);
     cfg->nee_blocks_per_cu = c->cfg.nee_bpc < 0 ? maxb : std::min(c->cfg.nee_bpc, maxb);
     cfg->photon_blocks_per_cu = c->cfg.photon_bpc;
@@ -4083,7 +4082,7 @@ extern "C" neb_status neb_autotune(neb_ctx c, int32_t trial_iterations, void* st
     for (int stack : {32, 48, 64}) {
         if (st != NEB_OK) break;
         if (stack <= c->forest_depth) continue;
-        int maxb = lds_blocks_per_cu(stack);
+        int maxb = trace_blocks_resident(stack);
         for (int b : {0, 4, 8, 12, 16, maxb}) {
             if (b > maxb) continue;
             neb_launch_config cfg{stack, b, -1, best.photon_blocks_per_cu, best.photon_order, best.concurrent};
@@ -4099,9 +4098,9 @@ extern "C" neb_status neb_autotune(neb_ctx c, int32_t trial_iterations, void* st
     }
     best_ms = 1e300;
     const int nee_k[1] = {K_NEE};
-    for (int b : {0, 4, 8, 12, 16, lds_blocks_per_cu(best.bvh_stack)}) {
+    for (int b : {0, 4, 8, 12, 16, trace_blocks_resident(best.bvh_stack)}) {
         if (st != NEB_OK) break;
-        if (b > lds_blocks_per_cu(best.bvh_stack)) continue;
+        if (b > trace_blocks_resident(best.bvh_stack)) continue;
         neb_launch_config cfg{best.bvh_stack, best.trace_blocks_per_cu, b, best.photon_blocks_per_cu,
                               best.photon_order, best.concurrent};
         double ms = 0.0;
@@ -4134,7 +4133,7 @@ extern "C" neb_status neb_autotune(neb_ctx c, int32_t trial_iterations, void* st
     c->prof_on = false;
     if (st == NEB_OK) {
         const neb_launch_config base = best;
-        const int maxb = lds_blocks_per_cu(base.bvh_stack);
+        const int maxb = trace_blocks_resident(base.bvh_stack);
         best_ms = 1e300;
         for (int order : {base.photon_order, 1 - base.photon_order})
             for (int tb : {base.trace_blocks_per_cu, 8, 10, 12, 16}) {

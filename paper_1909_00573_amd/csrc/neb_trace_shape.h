@@ -8,6 +8,18 @@ namespace neb {
 
 constexpr int kTraceBlock = 64;  // threads per traversal block (one wave)
 
+// LDS of a block: the lanes' stacks, and what lanes that share rays exchange
+// (per lane a nearest hit of 8 bytes, a count of 4, a donation of 8)
+constexpr int kTraceShareBytes = kTraceBlock * (8 + 4 + 8);
+constexpr int trace_lds_bytes(int stack) { return stack * kTraceBlock * 4 + kTraceShareBytes; }
+constexpr int kLdsBytes = 160 * 1024;  // of a CU
+// blocks that a CU's LDS holds: 17, 12 and 9 for stacks of 32, 48 and 64
+// entries (what hipOccupancyMaxActiveBlocksPerMultiprocessor says, too)
+constexpr int trace_blocks_resident(int stack) { return kLdsBytes / trace_lds_bytes(stack); }
+// blocks per CU that a launch configuration may name (20, 13 and 10: what the
+// stacks alone leave room for); launches have at most the resident ones
+constexpr int trace_blocks_accepted(int stack) { return kLdsBytes / (stack * kTraceBlock * 4); }
+
 // A queue of at most this many rays per wave of its launch is dealt out at once.
 constexpr int kDealRays = 16;
 

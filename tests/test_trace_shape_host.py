@@ -24,7 +24,7 @@ def shape(tmp_path_factory):
 
     def ask(*line):
         out = subprocess.run([exe], input=" ".join(map(str, line)), check=True, capture_output=True, text=True)
-        return int(out.stdout)
+        return out.stdout.split()
     return ask
 
 
@@ -32,7 +32,7 @@ def shape(tmp_path_factory):
     (1, 128, 48, 1), (65536, 128, 48, 1), (65537, 128, 48, 0), (4096, FOUR_GB - 1, FOUR_GB - 1, 1),
     (4096, FOUR_GB, 48, 0), (4096, 128, FOUR_GB, 0), (1 << 20, FOUR_GB, FOUR_GB, 0)])
 def test_deals_where_the_kernel_does(shape, npix, nodes, tris, deals):
-    assert shape("deals", npix, nodes, tris) == deals
+    assert shape("deals", npix, nodes, tris) == [str(deals)]
 
 
 @pytest.mark.parametrize("cap,bpc,deals,blocks", [
@@ -40,4 +40,12 @@ def test_deals_where_the_kernel_does(shape, npix, nodes, tris, deals):
     (0, 8, 0, 1), (1 << 20, -1, 0, 256 * 16), (1 << 20, 20, 0, 256 * 16), (4096, 0, 0, 64), (4096, 0, 1, 64),
     (1 << 27, 0, 0, 1 << 20)])
 def test_blocks(shape, cap, bpc, deals, blocks):
-    assert shape("blocks", 256, cap, bpc, 16, deals) == blocks
+    assert shape("blocks", 256, cap, bpc, 16, deals) == [str(blocks)]
+
+
+@pytest.mark.parametrize("stack,accepted", [(32, 20), (48, 13), (64, 10)])
+def test_resident_blocks_fit(shape, stack, accepted):
+    lds, resident, named = map(int, shape("lds", stack))
+    # stacks and 20 bytes a lane for shared rays
+    assert lds == stack * 256 + 1280 and lds * resident <= 160 * 1024 < lds * (resident + 1)
+    assert named == accepted  # what configurations could name before rays were shared
