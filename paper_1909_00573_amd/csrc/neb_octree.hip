@@ -548,7 +548,11 @@ hipError_t octree_insert_rounds(int32_t* nodes, int32_t* fresh, OctState* states
     }
     hipLaunchKernelGGL(k_oct_insert_tail, dim3(1), dim3(256), 0, s, nodes, fresh, states, prm, dyn, pos, stride,
                        scene_word, shift, defer[0], defer[1], cnt, n_host);
-    hipLaunchKernelGGL(k_oct_fold, dim3(512, n_trees), dim3(256), 0, s, nodes, fresh, states, prm, dyn, cnt, n_dev,
+    // 512 blocks for a tree, but in a batch about as many in all as are resident
+    // at once: with 512 for each of 256 small trees most blocks found nothing to
+    // do (256 scenes of 16 x 16 pixels 0.91 ms per iteration instead of 0.85)
+    const int fold = std::max(8, std::min(512, 2048 / n_trees));
+    hipLaunchKernelGGL(k_oct_fold, dim3(fold, n_trees), dim3(256), 0, s, nodes, fresh, states, prm, dyn, cnt, n_dev,
                        n_host);
     return hipGetLastError();
 }
