@@ -124,7 +124,8 @@ struct Grid {
                       // (n, tag), (wo, B), (tau, g), (pixel, -, -, -)
     int32_t* sums;    // scan block sums
     int32_t T;        // hash buckets (power of two)
-    int32_t D;        // depth classes: 2
+    int32_t D;        // depth classes
+    int32_t shift;    // 1 << shift depths per class (the last one also holds every deeper vertex)
 };
 
 // prefix sums are scanned in tiles of kScanTile elements (a tile per block
@@ -1407,9 +1408,10 @@ __global__ void __launch_bounds__(256) k_nee_recycle(RenderArgs A, VertexStore V
 // scan, which zeroes the counts for the next iteration -> scatter to
 // start[key] + rank)
 // ---------------------------------------------------------------------------
-// Depths 1 to 4 are one class, the deeper ones the other: a photon of the
-// later bounces, which may only merge with shallow vertices, skips the second.
-__device__ __forceinline__ int grid_class(const Grid& G, int depth) { return min((depth - 1) >> 2, G.D - 1); }
+// The depth classes let a photon of the later bounces, which may only merge
+// with shallow vertices, skip the others: depths 1 to 4 and the deeper ones, or
+// eight of a depth each (set_grid_classes).
+__device__ __forceinline__ int grid_class(const Grid& G, int depth) { return min((depth - 1) >> G.shift, G.D - 1); }
 __device__ __forceinline__ int64_t grid_key(const Grid& G, uint32_t h, int depth) {
     return (int64_t)h * G.D + grid_class(G, depth);
 }
@@ -1550,7 +1552,7 @@ static constexpr int64_t scan_scratch(int64_t n) { return n > 1 ? (n + kScanTile
 // exclusive prefix sum of n ints (in and out may alias unless zero_in):
 // tiles of 4096, then each tile adds the sums of the tiles before it, which
 // its block sums up itself.  A launch of one block that scanned the sums took
-// 5-6 us, and the largest table (16.8 M keys) has 4097 tiles, whose sums lie
+// 5-6 us, and the largest table (67 M keys) has 16385 tiles, whose sums lie
 // in L2: 3 001 fixed-radius queries, whose table is one
 // tile, 26.9 -> 20.2 us; a 64 x 64 preview 2 % faster.
 // zero_in clears the input as it is read.
@@ -2494,6 +2496,11 @@ static neb_status check_params(const neb_params* p) {
     return NEB_OK;
 }
 
+// frames that may get eight depth classes in the merge grid (set_grid_classes):
+// more vertex slots, and more vertices per merge disc
+constexpr uint64_t kCrowdedVertices = 1u << 23;
+constexpr double kCrowdedDisc = 20.0;
+
 extern "C" neb_status neb_create_batch(const neb_params* params, int32_t n_scenes, neb_ctx* out) {
     if (!params || !out) return fail(NEB_ERR_INVALID_ARG, "null pointer");
     *out = nullptr;
@@ -2613,8 +2620,10 @@ extern "C" neb_status neb_create_batch(const neb_params* params, int32_t n_scene
     // four 1567 / 483 / 700, two 1549 / 454 / 664, one 1595 / 441 / 670; grid
     // build 293 / 830 / 430, 277 / 623 / 398, 281 / 542 / 401, 272 / 493 / 401.
     // Half the buckets: room 1581, batch 689 (blocks share buckets).
+    // Larger, crowded frames get eight classes all the same (set_grid_classes).
     const uint64_t around = next_pow2((uint64_t)vcap);
-    c->G.D = 2;
+    c->G.D = (uint64_t)vcap > kCrowdedVertices ? 8 : 2;  // at most; set_grid_classes
+    c->G.shift = 2;
     c->G.T = (int32_t)std::max<uint64_t>(1024, std::min<uint64_t>(around, 1u << 23));
     const int32_t half = (int32_t)std::max<uint64_t>(1024, std::min<uint64_t>(around / 2, 1u << 23));
     int64_t gkeys = (int64_t)c->G.T * c->G.D + 1;
@@ -2900,6 +2909,36 @@ static neb_status restart(neb_ctx c, hipStream_t s) {
 // Concatenates the scenes into the shared pools (BVH forest with per-scene
 // roots, triangles, prim tables, materials, lights), writes the per-scene
 // tables and initialises the octrees.  Runs once after the scenes change.
+// Depth classes of the merge grid.  Where a hit has many vertices in reach, the
+// ones that it may not merge with cost more than the lines of a larger
+// table.  By vertices per merge disc, all vertices spread over the surfaces:
+// room 2048 x 2048 (114) merges 281 ms per iteration with two classes, 256
+// with eight, grid build 3.6 and 3.7; 1500 x 1500 (61) 80 and 75, 1.9 and 2.1; 1024
+// x 1024 (29) 18.5 and 17.4, 0.92 and 1.16; 512 x 512 (7) 1.55 and 1.62; city 2048
+// x 2048 (0.7) 4.2 and 4.5, 1.6 and 2.0.  The table's memory is taken for frames of
+// more than 2^23 vertices only.
+static void set_grid_classes(neb_ctx c) {
+    if ((uint64_t)c->vcap <= kCrowdedVertices) return;
+    double reach = 0.0;  // per vertex, of all scenes
+    for (int s = 0; s < c->n_scenes; ++s) {
+        const std::vector<float>& tris = c->hs[s].bvh.tris;
+        double area = 0.0;
+        for (size_t t = 0; t + 12 <= tris.size(); t += 12) {
+            double e[2][3];
+            for (int k = 0; k < 2; ++k)
+                for (int a = 0; a < 3; ++a) e[k][a] = (double)tris[t + 4 + 4 * k + a] - tris[t + a];
+            const double x = e[0][1] * e[1][2] - e[0][2] * e[1][1], y = e[0][2] * e[1][0] - e[0][0] * e[1][2],
+                         z = e[0][0] * e[1][1] - e[0][1] * e[1][0];
+            area += 0.5 * std::sqrt(x * x + y * y + z * z);
+        }
+        const double share = (double)(c->pix_base[s + 1] - c->pix_base[s]) / (double)c->npix, r = c->prm[s].merge_radius;
+        if (area > 0.0) reach += share * share * M_PI * r * r / area;
+    }
+    const bool crowded = (double)c->vcap * reach > kCrowdedDisc;
+    c->G.D = crowded ? 8 : 2;
+    c->G.shift = crowded ? 0 : 2;
+}
+
 static neb_status prepare(neb_ctx c) {
     if (c->ready) return NEB_OK;
     for (int s = 0; s < c->n_scenes; ++s)
@@ -3024,6 +3063,7 @@ static neb_status prepare(neb_ctx c) {
     c->tri_bytes = 48 * (n_tris + 1);
     // the shallowest stack that holds every tree's deepest descent
     if (c->cfg.stack <= depth) c->cfg.stack = depth < 32 ? 32 : (depth < 48 ? 48 : 64);
+    set_grid_classes(c);
     neb_status st = restart(c, nullptr);
     if (st != NEB_OK) return st;
     HIP_TRY(hipDeviceSynchronize());
