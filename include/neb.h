@@ -108,8 +108,11 @@ typedef struct {
                                      exceed the entries every scene's BVH needs (a node visit
                                      pushes all but the nearest of its inner children) */
     int32_t trace_blocks_per_cu;  /* resident closest-hit blocks (one wave each) per compute unit;
-                                     0 = one block per 64 queue slots, -1 = as many as the LDS holds;
-                                     a launch never has more blocks than one per 64 queue slots */
+                                     0 = one block per 64 queue slots, -1 = as many as the LDS holds
+                                     (17, 12 or 9 for the stack; up to 20, 13 or 10 may be asked for and
+                                     are taken as that); a launch never has more blocks than one per 64
+                                     queue slots, or per eight in contexts of at most 65 536 pixels, whose
+                                     short queues are dealt out a few rays to a block */
     int32_t nee_blocks_per_cu;    /* resident NEE (shadow-ray) blocks per compute unit, same
                                      conventions */
     int32_t photon_blocks_per_cu; /* photon-merge blocks (one wave each) per compute unit, 0..64;
@@ -511,8 +514,9 @@ neb_status neb_octree_create(const float scene_min[3], const float scene_max[3],
 neb_status neb_octree_set_iteration(neb_octree oct, int32_t iter);
 
 /* Deposits n points (device, n*3 floats) with lock-free counter
- * increments, compare-and-swap counting and on-the-fly splits (Sec. 5.1,
- * 5.2).  single_thread != 0 makes one GPU thread insert them in array
+ * increments (fetch-add into a second word per node) and on-the-fly splits
+ * (Sec. 5.1, 5.2).  What a call costs depends on its points, not on the size
+ * of the tree.  single_thread != 0 makes one GPU thread insert them in array
  * order (deterministic; equals a sequential insertion). */
 neb_status neb_octree_increment(neb_octree oct, const float* pos, int32_t n, int32_t single_thread,
                                 void* stream);

@@ -497,7 +497,9 @@ __device__ __forceinline__ float tri_hit(const RayPre& r, f3 v0, f3 v1, f3 v2, f
 // trace_triangle tests the triangles of the leaves among them one at a time,
 // slot by slot, before the next trace_node stacks the inner children still in
 // reach, nearest on top.  The order is that of a walk of one ray by itself.
-// Ties on t go to the lowest primitive id; the stack is the lane's LDS slots
+// Of the triangles tested, the lowest primitive id wins a tie on t; a child no
+// nearer than the nearest hit is dropped, so of triangles at one distance in
+// different leaves some may not be tested.  The stack is the lane's LDS slots
 // (stride kTraceBlock, slot 0 never filled).
 struct TraceState {
     RayPre r;

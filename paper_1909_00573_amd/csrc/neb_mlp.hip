@@ -283,7 +283,9 @@ __device__ __forceinline__ void stage_small(const float* __restrict__ theta, flo
 // Inference: out[i] = log rho (mode 0) or rho = exp(log rho) (mode 1).
 // Bound by instruction issue: 620 vector instructions per 16-sample tile (half
 // of them the ten sincospif of a lane) and 28 matrix products, 2 870 cycles per
-// tile and SIMD at 1.835 M samples, 163 -> 134 us.  Before: 906 instructions
+// tile and SIMD at 1.835 M samples, 163 -> 134 us (uniform random points and
+// normals; points on a few planes and a ball, whose operands change less from
+// sample to sample, 148 -> 110).  Before: 906 instructions
 // (rounding to bf16 in integers, selecting a pair's coordinate through five
 // compares, quieting NaNs before each ReLU).  Four waves per SIMD or two
 // measure the same; 2 048 blocks beat the 1 280 that are resident at once (141
