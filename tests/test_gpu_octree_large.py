@@ -73,12 +73,10 @@ def test_memory_is_there_from_the_start(neb):
     assert before - torch.cuda.mem_get_info()[0] < 64 << 20  # the queues of deferred points
 
 
-@pytest.mark.parametrize("single", [False, True])
-@pytest.mark.parametrize("iteration,n", [(250, 1), (250, 700), (1, 5000), (2, 60000)])
+@pytest.mark.parametrize("iteration,n,single", [(250, 1, False), (250, 700, False), (1, 5000, False), (2, 60000, False),
+                                                (250, 1, True), (250, 700, True), (1, 5000, True)])
 def test_waiting_counts_are_seen(neb, iteration, n, single):
     import torch
-    if single and n > 5000:
-        pytest.skip("one thread")
     t = _grown(neb, 8 << 20, 3000000, iteration)  # room for every split
     q = torch.cat([_points(20000, 9), _points(20000, 8, 0.4, 0.41)])
     nrm = torch.nn.functional.normalize(_points(40000, 7, -1.0, 1.0), dim=1)
