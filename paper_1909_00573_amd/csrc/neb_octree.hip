@@ -117,7 +117,7 @@ __device__ __forceinline__ void flush_tally(OctState* st, const SplitTally& T) {
 }
 
 // one deposit by one thread alone (sequential insertion, the oracle's order)
-__device__ __forceinline__ int oct_insert(int32_t* nodes, const int32_t* fresh, OctState* st, const OctParams& P,
+__device__ __forceinline__ int oct_insert(int32_t* nodes, const int32_t* unfolded, OctState* st, const OctParams& P,
                                           const OctDyn& D, f3 p) {
     float q[3];
     if (!oct_norm(P, p, q)) return kInsRejected;
@@ -131,7 +131,7 @@ __device__ __forceinline__ int oct_insert(int32_t* nodes, const int32_t* fresh, 
             v = ld_node(nodes + idx);
             continue;
         }
-        const int32_t cnt = oct_count(v, idx, oct_unfolded(*st, fresh));
+        const int32_t cnt = oct_count(v, idx, unfolded);
         bool can_split = !(v & kOctFailed) && level < kOctMaxDepth;
         if (can_split && cnt >= D.split_count) return kInsDeferred;
         int32_t expected = v;
@@ -399,12 +399,16 @@ __global__ void k_oct_insert_single(int32_t* nodes, const int32_t* fresh, OctSta
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
     const OctDyn D = *dyn;
     if (D.stop_filling) return;
+    int last = -1;  // the tree of the item before, and its fresh words if they count
+    const int32_t* unfolded = nullptr;
     for (int32_t i = 0; i < n; ++i) {
         int32_t item = order ? order[i] : i;
         if (item < 0) continue;
         const float* pp = pos + (size_t)stride * item;
         int s = item_scene(scene_word, stride, shift, item);
-        int r = oct_insert(nodes, fresh, states + s, prm[s], D, mk3(pp[0], pp[1], pp[2]));
+        if (s != last) unfolded = oct_unfolded(states[s], fresh);
+        last = s;
+        int r = oct_insert(nodes, unfolded, states + s, prm[s], D, mk3(pp[0], pp[1], pp[2]));
         if (r == kInsCounted) states[s].deposits[0].v += 1;
         if (r == kInsRejected) states[s].rejected += 1;
         if (r == kInsDeferred) states[s].lost += 1;  // impossible without concurrency
